@@ -172,6 +172,18 @@ size_t fsei_project_noalloc_max_bytes(void);
 fsei_status fsei_project_backward(fsei_plan* plan, double* gu, double* gv, double* gw, const double* gp,
                                   double dt);
 
+/* As fsei_project and fsei_project_backward, with the result in arrays of its
+ * own: the inputs are only read.  Each output is either its own input (in
+ * place) or an array that overlaps no input, no other output and not p. */
+fsei_status fsei_project_to(fsei_plan* plan, const double* u, const double* v, const double* w, double* u_out,
+                            double* v_out, double* w_out, double* p, double dt, fsei_info* info);
+fsei_status fsei_project_backward_to(fsei_plan* plan, const double* gu, const double* gv, const double* gw,
+                                     const double* gp, double* gu_out, double* gv_out, double* gw_out, double dt);
+fsei_status fsei_project_to_f32(fsei_plan* plan, const float* u, const float* v, const float* w, float* u_out,
+                                float* v_out, float* w_out, float* p, float dt);
+fsei_status fsei_project_backward_to_f32(fsei_plan* plan, const float* gu, const float* gv, const float* gw,
+                                         const float* gp, float* gu_out, float* gv_out, float* gw_out, float dt);
+
 /* FP32 variants (FSEI_PREC_FP32 plans), same conventions with float fields. */
 fsei_status fsei_project_f32(fsei_plan* plan, float* u, float* v, float* w, float* p, float dt);
 fsei_status fsei_project_backward_f32(fsei_plan* plan, float* gu, float* gv, float* gw, const float* gp,

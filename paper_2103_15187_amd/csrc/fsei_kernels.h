@@ -940,7 +940,10 @@ __global__ __launch_bounds__(256) void k_zero_mode(ZeroArgs<TS> a) {
 template <typename TIO, typename TP>
 struct GradArgs {
     int nx, ny, nz, bcx, bcy;
-    TIO* u;
+    const TIO* ui;   // velocity in; each the output below or an array that overlaps no output
+    const TIO* vi;
+    const TIO* wi;
+    TIO* u;          // velocity out
     TIO* v;
     TIO* w;
     const TP* p;
@@ -971,23 +974,38 @@ __global__ __launch_bounds__(256) void k_grad(GradArgs<TIO, TP> a) {
     }
     const long row = (long)k * ny + j;
     const size_t base = (size_t)row * nx;
-    TIO* __restrict__ u = a.u;
-    TIO* __restrict__ v = a.v;
-    TIO* __restrict__ w = a.w;
     const TP* __restrict__ p = a.p;
     const TIO bk = a.bk[k], gk = a.gk[k];
     const size_t jm = (j > 0) ? (size_t)nx : (size_t)0 - (size_t)(ny - 1) * nx;   // offset to row j-1
-#pragma unroll 4
-    for (int i = threadIdx.x; i < nx; i += 256) {
-        const size_t idx = base + i;
-        const TIO pc = (TIO)p[idx];
-        const TIO px = (TIO)p[(i > 0) ? idx - 1 : idx + nx - 1];
-        const TIO py = (TIO)p[idx - jm];
-        const TIO pz = (k > 0) ? (TIO)p[idx - (size_t)nx * ny] : (TIO)0;
-        const TIO uo = u[idx], vo = v[idx], wo = w[idx];
-        u[idx] = (a.bcx == FSEI_BC_WALL && i == 0) ? (TIO)0 : uo + a.cx * (pc - px);
-        v[idx] = (a.bcy == FSEI_BC_WALL && j == 0) ? (TIO)0 : vo + a.cy * (pc - py);
-        w[idx] = (k == 0) ? (TIO)0 : wo + a.sw * (bk * pc - gk * pz);
+    // four columns per thread and batch, every load before the first store
+    // (the outputs may be the inputs, so the compiler cannot move them)
+    constexpr int B = 4;
+    for (int i0 = threadIdx.x; i0 < nx; i0 += B * 256) {
+        TIO pc[B], px[B], py[B], pz[B], uo[B], vo[B], wo[B];
+#pragma unroll
+        for (int t = 0; t < B; ++t) {
+            const int i = i0 + t * 256;
+            if (i < nx) {
+                const size_t idx = base + i;
+                pc[t] = (TIO)p[idx];
+                px[t] = (TIO)p[(i > 0) ? idx - 1 : idx + nx - 1];
+                py[t] = (TIO)p[idx - jm];
+                pz[t] = (k > 0) ? (TIO)p[idx - (size_t)nx * ny] : (TIO)0;
+                uo[t] = a.ui[idx];
+                vo[t] = a.vi[idx];
+                wo[t] = a.wi[idx];
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < B; ++t) {
+            const int i = i0 + t * 256;
+            if (i < nx) {
+                const size_t idx = base + i;
+                a.u[idx] = (a.bcx == FSEI_BC_WALL && i == 0) ? (TIO)0 : uo[t] + a.cx * (pc[t] - px[t]);
+                a.v[idx] = (a.bcy == FSEI_BC_WALL && j == 0) ? (TIO)0 : vo[t] + a.cy * (pc[t] - py[t]);
+                a.w[idx] = (k == 0) ? (TIO)0 : wo[t] + a.sw * (bk * pc[t] - gk * pz[t]);
+            }
+        }
     }
 }
 
@@ -1017,12 +1035,12 @@ __global__ __launch_bounds__(NT) void k_grad_row2(GradArgs<TIO, TP> a) {
     const TP pxm = pr[im];
     const VP pyv = *reinterpret_cast<const VP*>(py + i);
     const VP pzv = *reinterpret_cast<const VP*>(pz + i);
-    TIO* __restrict__ u = a.u + ro;
-    TIO* __restrict__ v = a.v + ro;
-    TIO* __restrict__ w = a.w + ro;
-    const V uo = *reinterpret_cast<const V*>(u + i);
-    const V vo = *reinterpret_cast<const V*>(v + i);
-    const V wo = *reinterpret_cast<const V*>(w + i);
+    TIO* u = a.u + ro;
+    TIO* v = a.v + ro;
+    TIO* w = a.w + ro;
+    const V uo = *reinterpret_cast<const V*>(a.ui + ro + i);
+    const V vo = *reinterpret_cast<const V*>(a.vi + ro + i);
+    const V wo = *reinterpret_cast<const V*>(a.wi + ro + i);
     const TIO bk = a.bk[k], gk = a.gk[k];
     V un, vn, wn;
     un.x = (a.bcx == FSEI_BC_WALL && i == 0) ? (TIO)0 : uo.x + a.cx * ((TIO)pc.x - (TIO)pxm);
@@ -1151,7 +1169,10 @@ __global__ __launch_bounds__(NT) void k_resid_pairs(ResArgs<TPP> a) {
 // ---------------------------------------------------------------------------
 struct GradResArgs {
     int nx, ny, nz, bcx, bcy;
-    double* u;
+    const double* ui;     // velocity in (the outputs, or arrays that overlap none)
+    const double* vi;
+    const double* wi;
+    double* u;            // velocity out
     double* v;
     double* w;
     const double* p;      // current iterate (residual; gradient unless DELTA)
@@ -1185,9 +1206,12 @@ __global__ __launch_bounds__(NT) void k_grad_resid(GradResArgs a) {
     const float* __restrict__ ck = DELTA ? a.c + pl : nullptr;
     const float* __restrict__ ckm = (DELTA && k > 0) ? ck - nxy : ck;
     const double* __restrict__ fk = a.f + pl;
-    double* __restrict__ uk = a.u + pl;
-    double* __restrict__ vk = a.v + pl;
-    double* __restrict__ wk = a.w + pl;
+    const double* ui = a.ui + pl;
+    const double* vi = a.vi + pl;
+    const double* wi = a.wi + pl;
+    double* uk = a.u + pl;
+    double* vk = a.v + pl;
+    double* wk = a.w + pl;
     const double czm = (k > 0) ? a.za[k] : 0.0, czp = (k + 1 < nz) ? a.zc[k] : 0.0;
     const bool hzm = k > 0, hzp = k + 1 < nz;
     const bool pery = a.bcy == FSEI_BC_PERIODIC, perx = a.bcx == FSEI_BC_PERIODIC;
@@ -1220,9 +1244,9 @@ __global__ __launch_bounds__(NT) void k_grad_resid(GradResArgs a) {
                 pzm[r] = ld2d(pkm + ro + i);
                 pzp[r] = ld2d(pkp + ro + i);
                 fc[r] = ld2d(fk + ro + i);
-                uo[r] = ld2d(uk + ro + i);
-                vo[r] = ld2d(vk + ro + i);
-                wo[r] = ld2d(wk + ro + i);
+                uo[r] = ld2d(ui + ro + i);
+                vo[r] = ld2d(vi + ro + i);
+                wo[r] = ld2d(wi + ro + i);
                 if constexpr (DELTA) {
                     cc[r] = ld2d(ck + ro + i);
                     cxm[r] = (double)ck[ro + im];

@@ -1005,7 +1005,10 @@ struct XInvGradArgs {
     int ny, nz, bcx, bcy, kc;   // kc: planes per chunk
     const double* in;           // y-inverted field (transform space in x)
     double* p;                  // pressure out, or null
-    double* u;
+    const double* ui;           // velocity in (the outputs, or arrays that overlap none)
+    const double* vi;
+    const double* wi;
+    double* u;                  // velocity out
     double* v;
     double* w;
     double cx, cy, sw;
@@ -1126,9 +1129,9 @@ __global__ __launch_bounds__(xg_threads<NF>()) void k_xinv_grad(XInvGradArgs a) 
 #pragma unroll
                 for (int t = 0; t < GB; ++t) {
                     const size_t o = ro + (size_t)(l0 + t) * NF;
-                    uo[t] = *reinterpret_cast<const double2*>(a.u + o);
-                    vo[t] = *reinterpret_cast<const double2*>(a.v + o);
-                    wo[t] = *reinterpret_cast<const double2*>(a.w + o);
+                    uo[t] = *reinterpret_cast<const double2*>(a.ui + o);
+                    vo[t] = *reinterpret_cast<const double2*>(a.vi + o);
+                    wo[t] = *reinterpret_cast<const double2*>(a.wi + o);
                 }
 #pragma unroll
                 for (int t = 0; t < GB; ++t) {
@@ -1187,7 +1190,10 @@ struct XInvGradResArgs {
     const double* vsum;     // vsum[0] * vscale is subtracted from p32
     double vscale;
     double* p;              // pressure out (FP64)
-    double* u;
+    const double* ui;       // velocity in (the outputs, or arrays that overlap none)
+    const double* vi;
+    const double* wi;
+    double* u;              // velocity out
     double* v;
     double* w;
     double cx, cy, sw;
@@ -1339,9 +1345,9 @@ __global__ __launch_bounds__(xgr_threads<NF>()) void k_xinv_grad_resid(XInvGradR
                         const float* pr = a.p32 + (o - i);
                         qxm[t] = pr[ixm];
                         qxp[t] = pr[ixp];
-                        uo[t] = *reinterpret_cast<const double2*>(a.u + o);
-                        vo[t] = *reinterpret_cast<const double2*>(a.v + o);
-                        wo[t] = *reinterpret_cast<const double2*>(a.w + o);
+                        uo[t] = *reinterpret_cast<const double2*>(a.ui + o);
+                        vo[t] = *reinterpret_cast<const double2*>(a.vi + o);
+                        wo[t] = *reinterpret_cast<const double2*>(a.wi + o);
                         fo[t] = *reinterpret_cast<const double2*>(a.f + o);
                     }
                 }

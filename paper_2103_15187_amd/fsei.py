@@ -73,6 +73,10 @@ def lib():
         "fsei_project_backward": (I, [P, P, P, P, P, D]),
         "fsei_project_f32": (I, [P, P, P, P, P, ctypes.c_float]),
         "fsei_project_backward_f32": (I, [P, P, P, P, P, ctypes.c_float]),
+        "fsei_project_to": (I, [P, P, P, P, P, P, P, P, D, ctypes.POINTER(Info)]),
+        "fsei_project_backward_to": (I, [P, P, P, P, P, P, P, P, D]),
+        "fsei_project_to_f32": (I, [P, P, P, P, P, P, P, P, ctypes.c_float]),
+        "fsei_project_backward_to_f32": (I, [P, P, P, P, P, P, P, P, ctypes.c_float]),
         "fsei_viscous_solve": (I, [P, I, P, D]),
         "fsei_viscous_solve_add": (I, [P, I, P, P, D]),
         "fsei_momentum_rhs": (I, [P, P, P, P, P, P, P, P, P, P, D, D, D, D]),
@@ -253,6 +257,39 @@ class Plan:
             _check(lib().fsei_project_backward(self._h, _ptr(gu), _ptr(gv), _ptr(gw), _ptr(gp), float(dt)),
                    "fsei_project_backward")
 
+    def _project_to(self, u, v, w, dt):
+        """project with the result in new tensors: (u, v, w, p); the inputs are only read."""
+        import torch
+        f32 = self.precision == PREC_FP32
+        dtype = torch.float32 if f32 else torch.float64
+        src = [self._field(a, dtype, n) for a, n in ((u, "u"), (v, "v"), (w, "w"))]
+        out = [torch.empty_like(a) for a in src] + [torch.empty_like(src[0])]
+        self._stream()
+        args = (self._h, *(_ptr(a) for a in src), *(_ptr(a) for a in out))
+        if f32:
+            _check(lib().fsei_project_to_f32(*args, float(dt)), "fsei_project_f32")
+        else:
+            inf = Info()
+            self._status(lib().fsei_project_to(*args, float(dt), ctypes.byref(inf) if self._floor_ok() else None),
+                         "fsei_project", inf)
+        return tuple(out)
+
+    def _project_backward_to(self, gu, gv, gw, gp, dt):
+        """project_backward with the result in new tensors; the inputs are only read."""
+        import torch
+        f32 = self.precision == PREC_FP32
+        dtype = torch.float32 if f32 else torch.float64
+        src = [self._field(a, dtype, n) for a, n in ((gu, "gu"), (gv, "gv"), (gw, "gw"))]
+        gp = self._field(gp, dtype, "gp")
+        out = [torch.empty_like(a) for a in src]
+        self._stream()
+        args = (self._h, *(_ptr(a) for a in src), _ptr(gp), *(_ptr(a) for a in out), float(dt))
+        if f32:
+            _check(lib().fsei_project_backward_to_f32(*args), "fsei_project_backward_f32")
+        else:
+            _check(lib().fsei_project_backward_to(*args), "fsei_project_backward")
+        return tuple(out)
+
     def viscous_solve(self, q, component, beta):
         """In place: q <- dq with (I - beta Lx)(I - beta Ly)(I - beta Lz) dq = q
         for velocity component 0 (u), 1 (v) or 2 (w) (implicit viscous step)."""
@@ -350,6 +387,14 @@ def _info_dict(inf):
             "rhs_vmean_removed": inf.rhs_vmean_removed, "floor_reached": bool(inf.floor_reached)}
 
 
+def _readable(t):
+    """t where the kernels can read it as it is (packed, 16-byte aligned), else a copy."""
+    t = t.detach()
+    if t.is_contiguous() and t.data_ptr() % 16 == 0 and not t.is_neg():
+        return t
+    return t.clone()
+
+
 def _autograd_fn():
     import torch
 
@@ -358,11 +403,9 @@ def _autograd_fn():
 
         @staticmethod
         def forward(ctx, plan, dt, u, v, w):
-            uo, vo, wo = u.detach().clone(), v.detach().clone(), w.detach().clone()
-            p = plan.project(uo, vo, wo, dt=dt)
             ctx.plan = plan
             ctx.dt = dt
-            return uo, vo, wo, p
+            return plan._project_to(_readable(u), _readable(v), _readable(w), dt)
 
         @staticmethod
         def backward(ctx, gu, gv, gw, gp):
@@ -371,11 +414,9 @@ def _autograd_fn():
 
             def g(t):
                 return torch.zeros(plan.shape, dtype=like.dtype, device=like.device) if t is None \
-                    else t.detach().contiguous().clone()
-            a, b, c = g(gu), g(gv), g(gw)
+                    else _readable(t.detach().contiguous())
             gpc = None if gp is None else gp.detach().contiguous()
-            plan.project_backward(a, b, c, gpc, dt=ctx.dt)
-            return None, None, a, b, c
+            return None, None, *plan._project_backward_to(g(gu), g(gv), g(gw), gpc, ctx.dt)
 
     return ProjectFn
 
