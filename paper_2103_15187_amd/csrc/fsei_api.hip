@@ -12,6 +12,7 @@
 #include <vector>
 
 #include "fsei_kernels.h"
+#include "fsei_lengths.h"
 #include "fsei_plan.h"
 #include "fsei_viscous.h"
 #include "fsei_momentum.h"
@@ -140,10 +141,26 @@ bool pair_tiles(const fsei_plan* p) { return p->nx % 2 == 0 && p->ny % kPairRows
 bool aligned16(const void* q) { return reinterpret_cast<uintptr_t>(q) % 16 == 0; }
 bool al16(const void* q) { return q == nullptr || aligned16(q); }   // optional pointer
 
-// the fixed-length x kernels (NF = 512 or 768, four sequences = eight rows
-// per tile) need every tile of rows full and inside one z-plane
-bool x_fixed(const fsei_plan* p) {
-    return (p->nx == 512 || p->nx == 768) && nseq_x(p) == 4 && p->ny % (2 * nseq_x(p)) == 0;
+// the kernels compiled for length n, or null
+const LenOps* len_ops(int n) {
+    switch (n) {
+#define FSEI_CASE(n) \
+    case n: return &len_ops_##n();
+        FSEI_LENGTHS(FSEI_CASE)
+#undef FSEI_CASE
+        default: return nullptr;
+    }
+}
+
+// The compiled x kernels read and write even lengths as aligned column pairs
+// (odd lengths by single values): fields off the 16-byte alignment take the
+// kernels with the length from the arguments.
+const LenOps* x_ops(const fsei_plan* p, bool aligned) {
+    return (p->nx % 2 != 0 || aligned) ? len_ops(p->nx) : nullptr;
+}
+// their workgroups: tiles of x_len_rows rows of one plane
+long x_len_blocks(const fsei_plan* p, const LenOps* o) {
+    return (long)((p->ny + o->x_rows - 1) / o->x_rows) * p->nz;
 }
 
 hipStream_t S(const fsei_plan* p) { return (hipStream_t)p->stream; }
@@ -151,8 +168,9 @@ hipStream_t S(const fsei_plan* p) { return (hipStream_t)p->stream; }
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
+// returns the number of workgroups (with a.partials: of partial sums)
 template <typename TI, typename TO, int PRO>
-void launch_xfwd(fsei_plan* p, XFwdArgs<TI, TO> a, int slot) {
+long launch_xfwd(fsei_plan* p, XFwdArgs<TI, TO> a, int slot) {
     a.nx = p->nx;
     a.ny = p->ny;
     a.nz = p->nz;
@@ -164,20 +182,21 @@ void launch_xfwd(fsei_plan* p, XFwdArgs<TI, TO> a, int slot) {
     a.tws = tab<TO>(p, T_TWX_S);
     a.dctc = tab<TO>(p, T_DCTX_C);
     a.dcts = tab<TO>(p, T_DCTX_S);
-    const size_t dyn = 2 * p->nx * sizeof(TO);
-    // the fixed path reads and writes every field as aligned column pairs
     const bool al = al16(a.u) && al16(a.v) && al16(a.w) && al16(a.gp) && al16(a.f) && al16(a.p) &&
                     al16(a.p32) && al16(a.out) && al16(a.out_f);
     Timed t(p, slot);
-    const dim3 grid((unsigned)xblocks(p));
-    if (x_fixed(p) && al && p->nx == 512)
-        hipLaunchKernelGGL((k_xfwd<TI, TO, PRO, 2048, 256, 512>), grid, dim3(256), dyn, S(p), a);
-    else if (x_fixed(p) && al && p->nx == 768)
-        hipLaunchKernelGGL((k_xfwd<TI, TO, PRO, 3072, 384, 768>), grid, dim3(384), dyn, S(p), a);
-    else if (x_emax(p->nx) == 3072)
-        hipLaunchKernelGGL((k_xfwd<TI, TO, PRO, 3072, 384, 0>), grid, dim3(384), dyn, S(p), a);
+    if (const LenOps* o = x_ops(p, al)) {
+        const long nb = x_len_blocks(p, o);
+        o->xfwd<TI, TO>(PRO)(a, (unsigned)nb, S(p));
+        return nb;
+    }
+    const size_t dyn = 2 * p->nx * sizeof(TO);
+    const long nb = xblocks(p);
+    if (x_emax(p->nx) == 3072)
+        hipLaunchKernelGGL((k_xfwd<TI, TO, PRO, 3072, 384>), dim3((unsigned)nb), dim3(384), dyn, S(p), a);
     else
-        hipLaunchKernelGGL((k_xfwd<TI, TO, PRO, 2048, 256, 0>), grid, dim3(256), dyn, S(p), a);
+        hipLaunchKernelGGL((k_xfwd<TI, TO, PRO, 2048, 256>), dim3((unsigned)nb), dim3(256), dyn, S(p), a);
+    return nb;
 }
 
 template <typename T, typename TP, int EPI>
@@ -200,18 +219,18 @@ void launch_xinv(fsei_plan* p, const T* in, TP* out, int slot, const float* add3
     a.tws = tab<T>(p, T_TWX_S);
     a.dctc = tab<T>(p, T_DCTX_C);
     a.dcts = tab<T>(p, T_DCTX_S);
-    const size_t dyn = 2 * p->nx * sizeof(T);
     const bool al = al16(in) && al16(out) && al16(add32) && al16(keep);
     Timed t(p, slot);
+    if (const LenOps* o = x_ops(p, al)) {
+        o->xinv<T, TP>(EPI)(a, (unsigned)x_len_blocks(p, o), S(p));
+        return;
+    }
+    const size_t dyn = 2 * p->nx * sizeof(T);
     const dim3 grid((unsigned)xblocks(p));
-    if (x_fixed(p) && al && p->nx == 512)
-        hipLaunchKernelGGL((k_xinv<T, TP, EPI, 2048, 256, 512>), grid, dim3(256), dyn, S(p), a);
-    else if (x_fixed(p) && al && p->nx == 768)
-        hipLaunchKernelGGL((k_xinv<T, TP, EPI, 3072, 384, 768>), grid, dim3(384), dyn, S(p), a);
-    else if (x_emax(p->nx) == 3072)
-        hipLaunchKernelGGL((k_xinv<T, TP, EPI, 3072, 384, 0>), grid, dim3(384), dyn, S(p), a);
+    if (x_emax(p->nx) == 3072)
+        hipLaunchKernelGGL((k_xinv<T, TP, EPI, 3072, 384>), grid, dim3(384), dyn, S(p), a);
     else
-        hipLaunchKernelGGL((k_xinv<T, TP, EPI, 2048, 256, 0>), grid, dim3(256), dyn, S(p), a);
+        hipLaunchKernelGGL((k_xinv<T, TP, EPI, 2048, 256>), grid, dim3(256), dyn, S(p), a);
 }
 
 // The velocity a gradient correction reads and the one it writes: the same
@@ -289,11 +308,6 @@ void launch_xinv_grad(fsei_plan* p, const double* in, double* pout, const Vel<do
         hipLaunchKernelGGL((k_xinv_grad<512>), grid, dim3(xg_threads<512>()), 2 * 512 * sizeof(double), S(p), a);
 }
 
-// dynamic LDS of the compile-time-length y forward kernel: the FFT twiddles,
-// and for FP32 also the DCT post-twiddles
-template <typename T>
-size_t yfwd_dyn(int nf) { return (sizeof(T) == 4 ? 4 : 2) * (size_t)nf * sizeof(T); }
-
 // first refinement correction fused with the gradient and the convergence
 // check (FP32 correction, FP64 p): nx of a compiled length, whole 8-row
 // tiles, every field 16-byte aligned; returns the number of partials written
@@ -354,73 +368,14 @@ void launch_y_cfg(fsei_plan* p, YArgs<T> a, bool inverse) {
     if (a.nseq > kSeqLine) a.nseq -= a.nseq % kSeqLine;
     const int tx = 2 * a.nseq;
     a.ntile = (p->nx + tx - 1) / tx;
-    const unsigned nb = (unsigned)(a.ntile * p->nz);
+    const dim3 grid((unsigned)(a.ntile * p->nz));
     const size_t dyn = 2 * p->ny * sizeof(T);
-    // fixed-length variant: full tiles of the compile-time width, column
-    // pairs addressed as one aligned vector
-    constexpr int kPsF = yfwd_pad<T>();
-    // (an FP64 512 line always takes the 4096-element tile: the wider FP64
-    // configuration is not compiled for it)
-    constexpr bool kFix = y_fixed_ok(EMAX, NTHR, 512) && y_fixed_ok(EMAX, NTHR, 512, kPsF) &&
-                          tile_nseq(EMAX, 512, kPsF) == tile_nseq(EMAX, 512) &&
-                          (sizeof(T) == 4 || EMAX <= 4096);
-    const bool fix = kFix && p->ny == 512 && a.nseq == tile_nseq(EMAX, 512) && p->nx % tx == 0 &&
-                     reinterpret_cast<uintptr_t>(a.data) % (2 * sizeof(T)) == 0;
-    if (inverse) {
-        Timed t(p, K_YINV);
-        if constexpr (kFix) {
-            if (fix) {
-                hipLaunchKernelGGL((k_yinv<T, EMAX, NTHR, 512>), dim3(nb), dim3(NTHR), dyn, S(p), a);
-                return;
-            }
-        }
-        hipLaunchKernelGGL((k_yinv<T, EMAX, NTHR, 0>), dim3(nb), dim3(NTHR), dyn, S(p), a);
-    } else {
-        Timed t(p, K_YFWD);
-        if constexpr (kFix) {
-            if (fix) {
-                hipLaunchKernelGGL((k_yfwd<T, EMAX, NTHR, 512, kPsF>), dim3(nb), dim3(NTHR), yfwd_dyn<T>(512), S(p),
-                                   a);
-                return;
-            }
-        }
-        hipLaunchKernelGGL((k_yfwd<T, EMAX, NTHR, 0>), dim3(nb), dim3(NTHR), dyn, S(p), a);
-    }
+    if (inverse)
+        hipLaunchKernelGGL((k_yinv<T, EMAX, NTHR>), grid, dim3(NTHR), dyn, S(p), a);
+    else
+        hipLaunchKernelGGL((k_yfwd<T, EMAX, NTHR>), grid, dim3(NTHR), dyn, S(p), a);
 }
 
-// Compile-time length 768 in y: tiles of 64-byte row segments (4 FP64 /
-// 8 FP32 column pairs) in 768-thread workgroups, two workgroups per CU
-// (measured at 768 x 768 x 1024: 5-12 % faster than one workgroup of
-// 128-byte segments per CU, whose 105 KB tile leaves no second one room);
-// needs whole tiles and pair-aligned data.  Returns false where it does not
-// apply.
-template <typename T>
-bool launch_y768(fsei_plan* p, YArgs<T> a, bool inverse) {
-    constexpr int NF = 768, NTHR = 768;
-    constexpr int EMAX = (32 / (int)sizeof(T)) * NF;   // 64-B tile rows
-    constexpr int kPsF = yfwd_pad<T>();
-    static_assert(y_fixed_ok(EMAX, NTHR, NF) && y_fixed_ok(EMAX, NTHR, NF, kPsF) &&
-                      tile_nseq(EMAX, NF, kPsF) == tile_nseq(EMAX, NF) && tile_nseq(EMAX, NF) == EMAX / NF,
-                  "768 y tile");
-    constexpr int NSF = EMAX / NF;
-    if (p->ny != NF || p->nx % (2 * NSF) != 0 || reinterpret_cast<uintptr_t>(a.data) % (2 * sizeof(T)) != 0)
-        return false;
-    a.nseq = NSF;
-    a.ntile = p->nx / (2 * NSF);
-    const unsigned nb = (unsigned)(a.ntile * p->nz);
-    const size_t dyn = 2 * NF * sizeof(T);
-    if (inverse) {
-        Timed t(p, K_YINV);
-        hipLaunchKernelGGL((k_yinv<T, EMAX, NTHR, NF>), dim3(nb), dim3(NTHR), dyn, S(p), a);
-    } else {
-        Timed t(p, K_YFWD);
-        hipLaunchKernelGGL((k_yfwd<T, EMAX, NTHR, NF, kPsF>), dim3(nb), dim3(NTHR), yfwd_dyn<T>(NF), S(p), a);
-    }
-    return true;
-}
-
-// y tiles: the workgroup's LDS holds enough columns that every row segment
-// it loads or stores covers 128 B (16 doubles / 32 floats) when ny allows
 template <typename T>
 void launch_y(fsei_plan* p, T* data, bool inverse) {
     YArgs<T> a{};
@@ -434,19 +389,22 @@ void launch_y(fsei_plan* p, T* data, bool inverse) {
     a.tws = tab<T>(p, T_TWY_S);
     a.dctc = tab<T>(p, T_DCTY_C);
     a.dcts = tab<T>(p, T_DCTY_S);
-    if (launch_y768<T>(p, a, inverse)) return;
-    // complex elements of a tile whose row segments are 128 B; the tile
-    // (2 arrays, padded) plus the 2 ny twiddles must fit in the 160 KB of LDS
+    Timed t(p, inverse ? K_YINV : K_YFWD);
+    if (const LenOps* o = len_ops(p->ny)) {
+        const bool vec = p->nx % 2 == 0 && reinterpret_cast<uintptr_t>(data) % (2 * sizeof(T)) == 0;
+        const int tx = 2 * (sizeof(T) == 8 ? o->y_pairs_d : o->y_pairs_f);
+        a.ntile = (p->nx + tx - 1) / tx;
+        o->y<T>(inverse, vec)(a, (unsigned)(a.ntile * p->nz), S(p));
+        return;
+    }
+    // lengths below 16 and above 1024: the workgroup's LDS holds enough
+    // columns that a row segment covers 128 B (16 doubles / 32 floats) where
+    // the tile (2 arrays, padded) plus the 2 ny twiddles fit the 160 KB
     const long want = (long)(64 / sizeof(T)) * p->ny;
-    auto fits = [&](long emax) {
-        return 2L * lds_elems((int)emax) * (long)sizeof(T) + 2L * p->ny * (long)sizeof(T) <= 160L * 1024;
-    };
-    if (want <= 2048)
-        launch_y_cfg<T, 2048, 256>(p, a, inverse);
-    else if (want <= 4096 || !fits(8192))
-        launch_y_cfg<T, 4096, 512>(p, a, inverse);
-    else
-        launch_y_cfg<T, 8192, 1024>(p, a, inverse);
+    const bool fits = (2L * lds_elems(8192) + 2L * p->ny) * (long)sizeof(T) <= 160L * 1024;
+    if (want <= 2048) launch_y_cfg<T, 2048, 256>(p, a, inverse);
+    else if (sizeof(T) == 4 || fits) launch_y_cfg<T, 8192, 1024>(p, a, inverse);
+    else if constexpr (sizeof(T) == 8) launch_y_cfg<T, 4096, 512>(p, a, inverse);
 }
 
 // chunking of the z lines: P chunks of exactly L rows (L one of the compiled
@@ -929,10 +887,9 @@ fsei_status read_scalars(fsei_plan* p, double* host, int n) {
 // sums of the last xfwd pass with partials (sum v^2, sum v, sum dz_k v) into
 // scalars[off..off+2]; with `vmean`, also scalars[0] = the V-mean of v,
 // sum dz_k v / (nx ny lz)
-void reduce_partials(fsei_plan* p, int off, bool vmean = false, long nblk = -1) {
+void reduce_partials(fsei_plan* p, int off, long nblk, bool vmean = false) {
     Timed t(p, K_NORM);
     const double scale = 1.0 / ((double)p->nx * (double)p->ny * p->lz);
-    if (nblk < 0) nblk = xblocks(p);
     double* out = scalars(p) + off;
     double* mean = vmean ? scalars(p) : nullptr;
     if (nblk <= 4 * kSumGroups) {
@@ -977,12 +934,12 @@ fsei_status refine_solve(fsei_plan* p, XFwdArgs<double, float> first, double* p6
     first.out_f = f64;
     first.partials = partials(p);
     first.dzw = tab<double>(p, T_DZ);
-    launch_xfwd<double, float, PRO>(p, first, K_XFWD);
+    const long nfirst = launch_xfwd<double, float, PRO>(p, first, K_XFWD);
     // scalars[5..7] = sum f^2, sum f, sum dz_k f; scalars[0] = V-mean of f in
     // FP64 (the FP32 zero-mode solve removes its own FP32 mean to stay
     // compatible, but the residual must use the exact one: a constant left in
     // the residual is in the null space of L and no correction removes it)
-    reduce_partials(p, 5, true);
+    reduce_partials(p, 5, nfirst, true);
     launch_y<float>(p, w32, false);
     launch_z<float>(p, w32, 0, false);
     launch_y<float>(p, w32, true);
@@ -1021,7 +978,7 @@ fsei_status refine_solve(fsei_plan* p, XFwdArgs<double, float> first, double* p6
     bool converged = false;
     bool floor = false;      // a correction no longer halved the residual
     bool measured = false;   // rel belongs to the current iterate
-    long nres = -1;   // partials of the last residual pass (-1: the xfwd tiles)
+    long nres = 0;    // partials of the last residual pass
     // The first solve's residual norm is reduced into scalars[8..10] but not
     // read back on its own: it is fetched with the first corrected iterate's
     // norm, so the common one-correction case waits on the host once.  (A
@@ -1029,7 +986,7 @@ fsei_status refine_solve(fsei_plan* p, XFwdArgs<double, float> first, double* p6
     bool first_pending = false;
     double vmean = 0.0;
     auto residual_norm = [&]() -> fsei_status {
-        reduce_partials(p, 1, false, nres);   // scalars[1..3]: sum r^2, sum r, (sum dz_k p or 0)
+        reduce_partials(p, 1, nres);   // scalars[1..3]: sum r^2, sum r, (sum dz_k p or 0)
         double h[11];
         fsei_status st = read_scalars(p, h, first_pending ? 11 : 8);
         if (st != FSEI_OK) return st;
@@ -1061,21 +1018,19 @@ fsei_status refine_solve(fsei_plan* p, XFwdArgs<double, float> first, double* p6
                            : launch_resid_pairs(p, f64, (const double*)p64);
         } else {
             r.out = nullptr;
-            nres = -1;
-            launch_xfwd<double, float, PRO_RESID>(p, r, K_RESNORM);
+            nres = launch_xfwd<double, float, PRO_RESID>(p, r, K_RESNORM);
         }
     };
     auto resid_pass = [&]() {
-        nres = -1;
         if (p_in_32) {
             XFwdArgs<double, float> r32 = r;
             r32.p = nullptr;
             r32.p32 = p32;
             r32.out = w32;
-            launch_xfwd<double, float, PRO_RESID_F>(p, r32, K_RESID_XFWD);
+            nres = launch_xfwd<double, float, PRO_RESID_F>(p, r32, K_RESID_XFWD);
         } else {
             r.out = w32;
-            launch_xfwd<double, float, PRO_RESID>(p, r, K_RESID_XFWD);
+            nres = launch_xfwd<double, float, PRO_RESID>(p, r, K_RESID_XFWD);
         }
     };
     resid_pass();
@@ -1084,7 +1039,7 @@ fsei_status refine_solve(fsei_plan* p, XFwdArgs<double, float> first, double* p6
         // The last is its V-integral: the first correction subtracts the
         // V-mean it gives, so p is pinned in FP64 (later corrections are
         // solves of residuals, whose V-mean is zero).
-        reduce_partials(p, 8, false, nres);
+        reduce_partials(p, 8, nres);
         first_pending = p->rtol > 0.0;
     } else if (p->rtol > 0.0) {
         fsei_status st = residual_norm();

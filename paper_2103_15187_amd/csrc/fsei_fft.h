@@ -1,4 +1,5 @@
-// Batched mixed-radix (8/4/3/2) Stockham FFT in LDS for gfx950.
+// Batched mixed-radix Stockham FFT in LDS for gfx950: radices 8, 4, 3, 2 for
+// lengths taken from the arguments, 16, 12, 9, 8, 6, 4, 3, 2 for compiled lengths.
 //
 // A workgroup transforms `nseq` complex sequences of length N held in LDS as
 // split real/imaginary arrays.  Element n of sequence s sits at
@@ -12,8 +13,8 @@
 // bit-reversal pass.  A stage is done in place: every thread gathers all of
 // its butterflies into registers, the workgroup synchronises, then scatters.
 //
-// When the length is a compile-time constant (NF > 0) the stage loop is
-// unrolled with constant radices and strides, so no integer division remains.
+// For a compiled length (fft_fixed) the stage loop is unrolled with constant
+// radices and strides, so no integer division remains.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -112,12 +113,93 @@ __device__ __forceinline__ void dft3(T* xr, T* xi) {
     xi[2] = mi - SIGN * s3 * ur;
 }
 
+// cos and sin of 2 pi k / R for the inner twiddles of the composite radices
+__host__ __device__ constexpr double root_c(int R, int k) {
+    const int e = k * (144 / R);   // in units of 2 pi / 144
+    return e == 0     ? 1.0
+           : e == 9   ? 0.92387953251128675613   // 16: 1
+           : e == 12  ? 0.86602540378443864676   // 12: 1
+           : e == 16  ? 0.76604444311897803520   // 9: 1
+           : e == 18  ? 0.70710678118654752440   // 16: 2
+           : e == 24  ? 0.5                      // 6: 1, 12: 2
+           : e == 27  ? 0.38268343236508977173   // 16: 3
+           : e == 32  ? 0.17364817766693034885   // 9: 2
+           : e == 36  ? 0.0                      // 12: 3, 16: 4
+           : e == 48  ? -0.5                     // 6: 2, 12: 4
+           : e == 54  ? -0.70710678118654752440  // 16: 6
+           : e == 64  ? -0.93969262078590838405  // 9: 4
+           : e == 72  ? -1.0                     // 12: 6
+           : e == 81  ? -0.92387953251128675613  // 16: 9
+                      : 2.0;                     // not an inner twiddle
+}
+__host__ __device__ constexpr double root_s(int R, int k) {
+    const int e = k * (144 / R);
+    return e == 0     ? 0.0
+           : e == 9   ? 0.38268343236508977173
+           : e == 12  ? 0.5
+           : e == 16  ? 0.64278760968653932632
+           : e == 18  ? 0.70710678118654752440
+           : e == 24  ? 0.86602540378443864676
+           : e == 27  ? 0.92387953251128675613
+           : e == 32  ? 0.98480775301220805937
+           : e == 36  ? 1.0
+           : e == 48  ? 0.86602540378443864676
+           : e == 54  ? 0.70710678118654752440
+           : e == 64  ? 0.34202014332566873304
+           : e == 72  ? 0.0
+           : e == 81  ? -0.38268343236508977173
+                      : 2.0;
+}
+
+template <typename T, int R, int SIGN>
+__device__ __forceinline__ void dftR(T* xr, T* xi);
+
+// radix A B: A-point DFTs over the elements n = B n1 + n2 of each n2, the
+// twiddles exp(SIGN 2 pi i n2 k1 / (A B)), B-point DFTs over n2; output
+// k1 + A k2
+template <typename T, int A, int B, int SIGN>
+__device__ __forceinline__ void dft_ab(T* xr, T* xi) {
+    constexpr int R = A * B;
+    T tr[B][A], ti[B][A];
+#pragma unroll
+    for (int n2 = 0; n2 < B; ++n2) {
+#pragma unroll
+        for (int n1 = 0; n1 < A; ++n1) {
+            tr[n2][n1] = xr[B * n1 + n2];
+            ti[n2][n1] = xi[B * n1 + n2];
+        }
+        dftR<T, A, SIGN>(tr[n2], ti[n2]);
+#pragma unroll
+        for (int k1 = 1; k1 < A; ++k1)
+            if (n2 > 0) cmul(tr[n2][k1], ti[n2][k1], (T)root_c(R, n2 * k1), (T)SIGN * (T)root_s(R, n2 * k1));
+    }
+#pragma unroll
+    for (int k1 = 0; k1 < A; ++k1) {
+        T vr[B], vi[B];
+#pragma unroll
+        for (int n2 = 0; n2 < B; ++n2) {
+            vr[n2] = tr[n2][k1];
+            vi[n2] = ti[n2][k1];
+        }
+        dftR<T, B, SIGN>(vr, vi);
+#pragma unroll
+        for (int k2 = 0; k2 < B; ++k2) {
+            xr[k1 + A * k2] = vr[k2];
+            xi[k1 + A * k2] = vi[k2];
+        }
+    }
+}
+
 template <typename T, int R, int SIGN>
 __device__ __forceinline__ void dftR(T* xr, T* xi) {
     if constexpr (R == 2) dft2<T, SIGN>(xr, xi);
     else if constexpr (R == 3) dft3<T, SIGN>(xr, xi);
     else if constexpr (R == 4) dft4<T, SIGN>(xr, xi);
-    else dft8<T, SIGN>(xr, xi);
+    else if constexpr (R == 6) dft_ab<T, 3, 2, SIGN>(xr, xi);
+    else if constexpr (R == 8) dft8<T, SIGN>(xr, xi);
+    else if constexpr (R == 9) dft_ab<T, 3, 3, SIGN>(xr, xi);
+    else if constexpr (R == 12) dft_ab<T, 4, 3, SIGN>(xr, xi);
+    else dft_ab<T, 4, 4, SIGN>(xr, xi);
 }
 
 // One Stockham stage of radix R over all nseq sequences.  MAXB bounds the
@@ -175,31 +257,42 @@ __device__ __forceinline__ void fft_stage(T* __restrict__ re, T* __restrict__ im
 
 __host__ __device__ constexpr int cdiv(int a, int b) { return (a + b - 1) / b; }
 
-// radix schedule shared with the host plan: 8s, then a 4 or a 2, then 3s
-__host__ __device__ constexpr int pow2_part(int n) { return (n % 3 == 0) ? pow2_part(n / 3) : n; }
+// Radix schedule of a compiled length: the fewest stages (each costs an LDS
+// round trip of the tile and two barriers), among those the smallest sum of
+// radices; powers of two first, the larger first (the first stage has no
+// twiddles, and scatters with the stride of its radix: 768 points as 12 8 8
+// instead of 8 8 12 took 3-5 % longer).
+constexpr int kNoSchedule = 1 << 20;
+__host__ __device__ constexpr int sched_cost(int n, int stages) {
+    if (stages == 0) return n == 1 ? 0 : kNoSchedule;
+    constexpr int rad[8] = {16, 12, 9, 8, 6, 4, 3, 2};
+    int best = kNoSchedule;
+    for (int r : rad)
+        if (n % r == 0) {
+            const int c = r + sched_cost(n / r, stages - 1);
+            if (c < best) best = c;
+        }
+    return best;
+}
 __host__ __device__ constexpr int num_stages(int n) {
-    int m = pow2_part(n), c = 0;
-    int r3 = 0;
-    for (int t = n; t % 3 == 0; t /= 3) ++r3;
-    while (m >= 8 && m % 8 == 0) {
-        m /= 8;
-        ++c;
-    }
-    if (m == 4 || m == 2) ++c;
-    return c + r3;
+    int s = 1;
+    while (sched_cost(n, s) >= kNoSchedule) ++s;
+    return s;
 }
 __host__ __device__ constexpr int stage_radix(int n, int st) {
-    int m = pow2_part(n), c = 0;
-    while (m >= 8 && m % 8 == 0) {
-        if (c == st) return 8;
-        m /= 8;
-        ++c;
+    constexpr int rad[8] = {16, 8, 4, 2, 12, 9, 6, 3};
+    int left = num_stages(n);
+    for (;;) {
+        const int want = sched_cost(n, left);
+        for (int r : rad)
+            if (n % r == 0 && r + sched_cost(n / r, left - 1) == want) {
+                if (st == 0) return r;
+                n /= r;
+                break;
+            }
+        --st;
+        --left;
     }
-    if (m == 4 || m == 2) {
-        if (c == st) return m;
-        ++c;
-    }
-    return 3;
 }
 
 template <typename T, int EMAX, int NTHR, int SIGN, int NF, int ST, int NS, int PS = kPadShift>
@@ -212,27 +305,24 @@ __device__ __forceinline__ void fft_fixed(T* re, T* im, int nseq, const T* __res
     }
 }
 
-// Full transform of nseq sequences (nseq*N <= EMAX) with NTHR threads.
-template <typename T, int EMAX, int NTHR, int SIGN, int NF, int PS = kPadShift>
+// Full transform of nseq sequences (nseq*N <= EMAX) with NTHR threads, the
+// length from the arguments.
+template <typename T, int EMAX, int NTHR, int SIGN>
 __device__ __forceinline__ void fft_lds(T* re, T* im, int N, int nseq, const FftPlan& pl,
                                         const T* __restrict__ twc, const T* __restrict__ tws) {
-    if constexpr (NF > 0) {
-        fft_fixed<T, EMAX, NTHR, SIGN, NF, 0, 1, PS>(re, im, nseq, twc, tws);
-    } else {
-        const int SP = seq_stride(N, PS);
-        int Ns = 1;
-        for (int st = 0; st < pl.nstages; ++st) {
-            const int R = pl.radix[st];
-            if (R == 8)
-                fft_stage<T, 8, cdiv(EMAX, NTHR * 8), SIGN, NTHR, PS>(re, im, N, SP, nseq, Ns, twc, tws);
-            else if (R == 4)
-                fft_stage<T, 4, cdiv(EMAX, NTHR * 4), SIGN, NTHR, PS>(re, im, N, SP, nseq, Ns, twc, tws);
-            else if (R == 2)
-                fft_stage<T, 2, cdiv(EMAX, NTHR * 2), SIGN, NTHR, PS>(re, im, N, SP, nseq, Ns, twc, tws);
-            else
-                fft_stage<T, 3, cdiv(EMAX, NTHR * 3), SIGN, NTHR, PS>(re, im, N, SP, nseq, Ns, twc, tws);
-            Ns *= R;
-        }
+    const int SP = seq_stride(N);
+    int Ns = 1;
+    for (int st = 0; st < pl.nstages; ++st) {
+        const int R = pl.radix[st];
+        if (R == 8)
+            fft_stage<T, 8, cdiv(EMAX, NTHR * 8), SIGN, NTHR>(re, im, N, SP, nseq, Ns, twc, tws);
+        else if (R == 4)
+            fft_stage<T, 4, cdiv(EMAX, NTHR * 4), SIGN, NTHR>(re, im, N, SP, nseq, Ns, twc, tws);
+        else if (R == 2)
+            fft_stage<T, 2, cdiv(EMAX, NTHR * 2), SIGN, NTHR>(re, im, N, SP, nseq, Ns, twc, tws);
+        else
+            fft_stage<T, 3, cdiv(EMAX, NTHR * 3), SIGN, NTHR>(re, im, N, SP, nseq, Ns, twc, tws);
+        Ns *= R;
     }
 }
 

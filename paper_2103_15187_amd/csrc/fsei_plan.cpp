@@ -61,6 +61,10 @@ void compute_layout(fsei_plan_impl* p) {
     // residual-norm pass, whichever is more
     p->n_partials = (size_t)std::max(((long)p->ny * p->nz + 2 * nseq - 1) / (2 * nseq),
                                      (long)((p->ny + 7) / 8) * p->nz);
+    if (p->nx <= kLenMax) {
+        const int nl = x_len_rows(p->nx);
+        p->n_partials = std::max(p->n_partials, (size_t)((p->ny + nl - 1) / nl) * p->nz);
+    }
 
     size_t off = 0;
     p->ws_tab_d = off;

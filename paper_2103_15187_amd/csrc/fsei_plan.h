@@ -35,6 +35,57 @@ constexpr int tile_nseq(int emax, int N, int ps = kPadShift) {
 }
 inline int x_nseq(int nx) { return tile_nseq(x_emax(nx), nx) > 0 ? tile_nseq(x_emax(nx), nx) : 1; }
 
+// Lengths with kernels compiled for them (fsei_len.hip): every 2^a 3^b from
+// kLenMin to kLenMax, as listed in FSEI_LENGTHS; other lengths, and fields
+// that are not aligned to column pairs, take the kernels with the length from
+// the arguments.
+constexpr int kLenMin = 16;
+constexpr int kLenMax = 1024;
+#define FSEI_LENGTHS(X)                                                                                     \
+    X(16) X(18) X(24) X(27) X(32) X(36) X(48) X(54) X(64) X(72) X(81) X(96) X(108) X(128) X(144) X(162)     \
+    X(192) X(216) X(243) X(256) X(288) X(324) X(384) X(432) X(486) X(512) X(576) X(648) X(729) X(768) X(864) \
+    X(972) X(1024)
+
+// Tile of the compiled x kernels: RG groups of threads, one thread per column
+// pair of the line in each, side by side over x_len_rows rows of one z-plane;
+// enough groups that the whole waves are at least 3/4 used, or as well used
+// as they can be.  A group takes up to eight rows (the same number of complex
+// elements per thread as a radix-8 butterfly), fewer where the groups are
+// many (short lines: small grids need the workgroups) or the line is long
+// (two FP64 workgroups of 1024-point lines must fit the CU's LDS).
+//
+// Threads (x and y): where LDS leaves two or three workgroups per CU, whole
+// sets of four waves, one per SIMD; a workgroup of five, six, seven, nine or
+// eleven waves loads the SIMDs unevenly and streams up to 40 % slower
+// (measured at 80 M cells, TB/s: y FP64 384 points 6 waves 3.3, 8 waves 5.5;
+// y FP32 432 points 14 waves 2.7, 16 waves 4.5; x FP64 768 points 6 waves
+// 3.9, 8 waves 4.9).  FP32 x tiles leave room for four and more workgroups, which
+// balance by themselves (768 points: 6 waves 4.36, 8 waves 4.17).
+constexpr int round64(int n) { return (n + 63) / 64 * 64; }
+constexpr int round_waves(int threads) { return threads <= 256 ? round64(threads) : (threads + 255) / 256 * 256; }
+constexpr int x_len_groups(int n) {
+    const int np = (n + 1) / 2;
+    int best = 1;
+    for (int rg = 1; rg <= 8; rg *= 2) {
+        if (4 * np * rg >= 3 * round64(np * rg)) return rg;
+        if (np * rg * round64(np * best) > np * best * round64(np * rg)) best = rg;
+    }
+    return best;
+}
+constexpr int x_len_rows(int n) { return x_len_groups(n) > 1 ? 16 : n > 768 ? 4 : 8; }
+constexpr int x_len_threads(int n, int elem) {
+    const int t = (n + 1) / 2 * x_len_groups(n);
+    return (elem == 4 && n <= 768) ? round64(t) : round_waves(t);
+}
+
+// Tile of the compiled y kernels: column pairs per tile (rows of 128 bytes;
+// 64 for lines beyond 512, two of whose workgroups then fit a CU), about
+// eight complex elements per thread
+constexpr int y_len_pairs(int n, int elem) { return (n <= 512 ? 64 : 32) / elem; }
+constexpr int y_len_threads(int n, int elem) { return round_waves(y_len_pairs(n, elem) * n / 8); }
+// waves per SIMD that two workgroups per CU need (the kernels' register bound)
+constexpr int y_len_waves(int n, int elem) { return (2 * y_len_threads(n, elem) + 255) / 256; }
+
 // Line solves of the implicit viscous step: every line is cut into
 // kViscPmax chunks of L rows (L one of the compiled sizes), so lines of up
 // to kViscPmax * 32 rows are supported.  One table block per (component,

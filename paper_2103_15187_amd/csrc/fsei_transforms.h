@@ -12,11 +12,11 @@
 // m at row N-m).  Both inverses are unnormalised (they return N times the
 // input); the z solve folds in the factor 1/(nx ny).
 //
-// Every kernel has an optional compile-time length NF (0 = taken from the
-// arguments): with NF fixed the FFT stages and all index arithmetic fold to
-// constants.  Tile loops have compile-time trip counts and are unrolled, so
-// a thread issues all loads of a batch before the first wait; addresses are
-// 32-bit offsets from per-workgroup base pointers.
+// The kernels here take the length from the arguments: they serve the lengths
+// below 16 and above 1024 and fields that are not aligned to column pairs; the
+// other lengths have kernels compiled for them (fsei_lengths.h).  Tile loops
+// have compile-time trip counts and are unrolled; addresses are 32-bit offsets
+// from per-workgroup base pointers.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -206,54 +206,6 @@ __device__ __forceinline__ void row_kj(int k0, int j0, int l, int ny, int& k, in
     }
 }
 
-// ---------------------------------------------------------------------------
-// Fixed-length full-tile paths.  The variants with NF > 0 are launched only
-// when every tile is full (the host checks), so each thread's rows, columns
-// and LDS slots are compile-time functions of its lane: loads and stores
-// address a workgroup-uniform row pointer (scalar registers) plus the lane's
-// 32-bit column, and every boundary test is either per row (uniform) or per
-// lane and fixed for the whole launch.  No bounds test remains in the loops.
-// ---------------------------------------------------------------------------
-
-// neighbour rows of x-row (k, j): element offsets from the row and whether
-// the neighbour takes part (a wall has no neighbour beyond it; an absent
-// neighbour's offset is 0 so its load stays in bounds and is discarded)
-struct RowNb {
-    long yp, ym, zp, zm;
-    bool hyp, hym, hzp, hzm;
-};
-__device__ __forceinline__ RowNb row_nb(int k, int j, int N, int ny, int nz, int bcy) {
-    const bool per = bcy == FSEI_BC_PERIODIC;
-    const long plane = (long)N * ny;
-    RowNb r;
-    r.hyp = (j + 1 < ny) || per;
-    r.yp = (j + 1 < ny) ? (long)N : (per ? -(long)(ny - 1) * N : 0L);
-    r.hym = (j >= 1) || per;
-    r.ym = (j >= 1) ? -(long)N : (per ? (long)(ny - 1) * N : 0L);
-    r.hzp = k + 1 < nz;
-    r.zp = r.hzp ? plane : 0L;
-    r.hzm = k >= 1;
-    r.zm = r.hzm ? -plane : 0L;
-    return r;
-}
-
-// x neighbours of column i: wrapped indices (always in [0, N)) and whether
-// they take part
-struct ColNb {
-    unsigned i, ip, im;
-    bool hip, him;
-};
-__device__ __forceinline__ ColNb col_nb(int i, int N, int bcx) {
-    const bool per = bcx == FSEI_BC_PERIODIC;
-    ColNb c;
-    c.i = (unsigned)i;
-    c.ip = (i + 1 < N) ? (unsigned)(i + 1) : 0u;
-    c.im = (i >= 1) ? (unsigned)(i - 1) : (unsigned)(N - 1);
-    c.hip = (i + 1 < N) || per;
-    c.him = (i >= 1) || per;
-    return c;
-}
-
 // forward post-processing from the four values at rows m and mm = (N - m) % N
 // of one pair (selects instead of branches; same arithmetic as post_fwd)
 template <typename T>
@@ -270,14 +222,7 @@ __device__ __forceinline__ void post_fwd_v(int bc, bool lo, T zr, T zi, T cr, T 
     }
 }
 
-// whether the fixed y tile of EMAX elements and NTHR threads at length NF
-// gives every thread whole column pairs on an even number of rows per pass
-__host__ __device__ constexpr bool y_fixed_ok(int emax, int nthr, int nf, int ps = kPadShift) {
-    return tile_nseq(emax, nf, ps) > 0 && nthr % tile_nseq(emax, nf, ps) == 0 &&
-           nf % (nthr / tile_nseq(emax, nf, ps)) == 0 && (nthr / tile_nseq(emax, nf, ps)) % 2 == 0;
-}
-
-// LDS pad of the fixed-length y forward kernel: FP32 tiles run fastest with
+// LDS pad of the compiled-length y forward kernels: FP32 tiles run fastest with
 // one pad slot per 64 elements, FP64 tiles with one per 16 (measured)
 template <typename T>
 constexpr int yfwd_pad() { return sizeof(T) == 4 ? 6 : kPadShift; }
@@ -317,7 +262,7 @@ struct Vec2T<float> {
 // RESID: the FP64 residual (f - mean) - L p of an FP64 iterate p; RESID_F: of
 // an FP32 iterate p32 (the first solve of the refinement), read as FP32 and
 // evaluated in FP64
-enum { PRO_COPY = 0, PRO_DIV = 1, PRO_DIV_ADJ = 2, PRO_RESID = 3, PRO_RESID_F = 5 };
+enum { PRO_COPY = 0, PRO_DIV = 1, PRO_DIV_ADJ = 2, PRO_RESID = 3, PRO_RESID_F = 4, PRO_KINDS = 5 };
 
 template <typename TI, typename TO>
 struct XFwdArgs {
@@ -355,13 +300,6 @@ template <int PRO, typename TI, typename TO>
 __device__ __forceinline__ auto resid_iterate(const XFwdArgs<TI, TO>& a) {
     if constexpr (PRO == PRO_RESID_F) return a.p32;
     else return a.p;
-}
-
-// two adjacent values as a double2 (from double2 or float2)
-__device__ __forceinline__ double2 pair_d(const double* q) { return *reinterpret_cast<const double2*>(q); }
-__device__ __forceinline__ double2 pair_d(const float* q) {
-    const float2 v = *reinterpret_cast<const float2*>(q);
-    return make_double2((double)v.x, (double)v.y);
 }
 
 // The stencil value at cell (k, j, i); `o` is the cell's offset from the
@@ -410,320 +348,62 @@ __device__ __forceinline__ TI x_prologue(const XFwdArgs<TI, TO>& a, size_t base,
     }
 }
 
-// x neighbours of the adjacent cells (i, i + 1), i even: i - 1 of the first
-// and i + 2 of the second (wrapped; the flags say whether they take part)
-struct PairNb {
-    unsigned i, im, ip2;
-    bool him, hip2;
-};
-__device__ __forceinline__ PairNb pair_nb(int i, int N, int bcx) {
-    const bool per = bcx == FSEI_BC_PERIODIC;
-    PairNb c;
-    c.i = (unsigned)i;
-    c.im = (i >= 1) ? (unsigned)(i - 1) : (unsigned)(N - 1);
-    c.ip2 = (i + 2 < N) ? (unsigned)(i + 2) : 0u;
-    c.him = (i >= 1) || per;
-    c.hip2 = (i + 2 < N) || per;
-    return c;
-}
-
-// The divergence / copy prologue for the two adjacent cells (i, i + 1) of a
-// row, every field read as aligned pairs (the scalar x neighbour aside); the
-// residual prologue of the compile-time-length path is written out in
-// k_xfwd (it carries the iterate's rows down the tile)
-template <typename TI, typename TO, int PRO>
-__device__ __forceinline__ void x_prologue_pair(const XFwdArgs<TI, TO>& a, size_t ro, int k, const RowNb& rn,
-                                                const PairNb& cn, TI& v0, TI& v1) {
-    using V = typename Vec2T<TI>::type;
-    if constexpr (PRO == PRO_COPY) {
-        const double2 f = *reinterpret_cast<const double2*>(a.f + ro + cn.i);
-        v0 = (TI)f.x;
-        v1 = (TI)f.y;
-    } else {
-        const TI zero = (TI)0;
-        const TI* __restrict__ u = a.u + ro;
-        const TI* __restrict__ v = a.v + ro;
-        const TI* __restrict__ w = a.w + ro;
-        const V uc = *reinterpret_cast<const V*>(u + cn.i);
-        const TI uh = u[cn.ip2];
-        const V vc = *reinterpret_cast<const V*>(v + cn.i);
-        const V vh = *reinterpret_cast<const V*>(v + rn.yp + cn.i);
-        const V wc = *reinterpret_cast<const V*>(w + cn.i);
-        const V wh = *reinterpret_cast<const V*>(w + rn.zp + cn.i);
-        const TI zk = a.zeta[k], ek = a.eta[k];
-        TI r0 = (uc.y - (cn.him ? uc.x : zero)) * a.idx + ((rn.hyp ? vh.x : zero) - (rn.hym ? vc.x : zero)) * a.idy +
-                (zk * (rn.hzp ? wh.x : zero) - ek * (rn.hzm ? wc.x : zero));
-        TI r1 = ((cn.hip2 ? uh : zero) - uc.y) * a.idx + ((rn.hyp ? vh.y : zero) - (rn.hym ? vc.y : zero)) * a.idy +
-                (zk * (rn.hzp ? wh.y : zero) - ek * (rn.hzm ? wc.y : zero));
-        r0 *= a.alpha;
-        r1 *= a.alpha;
-        if constexpr (PRO == PRO_DIV_ADJ) {
-            if (a.gp) {
-                const V g = *reinterpret_cast<const V*>(a.gp + ro + cn.i);
-                r0 += a.beta * g.x;
-                r1 += a.beta * g.y;
-            }
-        }
-        v0 = r0;
-        v1 = r1;
-    }
-}
-
-template <typename TI, typename TO, int PRO, int EMAX, int NTHR, int NF>
+template <typename TI, typename TO, int PRO, int EMAX, int NTHR>
 __global__ __launch_bounds__(NTHR) void k_xfwd(XFwdArgs<TI, TO> a) {
     __shared__ TO sre[lds_elems(EMAX)];
     __shared__ TO sim[lds_elems(EMAX)];
     __shared__ double sred[3 * (NTHR / 64)];
-    constexpr int NSF = NF > 0 ? tile_nseq(EMAX, NF) : 0;   // pairs per tile, fixed path
-    const int N = NF > 0 ? NF : a.nx;
+    const int N = a.nx;
     const int SP = seq_stride(N);
-    const int nseq = NF > 0 ? NSF : a.nseq;
+    const int nseq = a.nseq;
     const int nl = 2 * nseq;
     const long nrows = (long)a.ny * a.nz;
-    long row0;
-    int k0, j0;
-    if constexpr (NF > 0) {
-        // tiles in (row tile, plane) order, plane fastest: the tile of the
-        // same rows one plane up, whose rows of w (or p) this tile also
-        // reads, is the next workgroup on the same XCD (an L2 hit)
-        const int b = (int)xcd_remap(blockIdx.x, gridDim.x);
-        const int jt = b / a.nz;
-        k0 = b - jt * a.nz;
-        j0 = jt * nl;
-        row0 = (long)k0 * a.ny + j0;
-    } else {
-        row0 = xcd_remap(blockIdx.x, gridDim.x) * nl;
-        k0 = (int)(row0 / a.ny);
-        j0 = (int)(row0 - (long)k0 * a.ny);
-    }
+    const long row0 = xcd_remap(blockIdx.x, gridDim.x) * nl;
+    const int k0 = (int)(row0 / a.ny);
+    const int j0 = (int)(row0 - (long)k0 * a.ny);
     const size_t base = (size_t)row0 * N;
-    TO* twl = lds_twiddle_ptr<TO>();
-    TwiddleRegs<TO, NTHR, (NF > 0 ? NF : 1)> twr;
-    if constexpr (NF == 0) stage_twiddles<TO, NTHR>(twl, a.twc, a.tws, N);
-    else twr.load(a.twc, a.tws);
+    TO* twl = lds_twiddles<TO, NTHR>(a.twc, a.tws, N);
     double* __restrict__ out_f = a.out_f;
-    constexpr int PPW = NF > 0 ? NF / NTHR / 2 : 1;
-    TO pw[PPW][4];   // fixed path: post-twiddles (cos, sin) of outputs i and i + 1
-    double ss = 0.0, s1 = 0.0, s2 = 0.0, sp = 0.0;
-    if constexpr (NF > 0) {
-        static_assert(NF % NTHR == 0, "fixed x path: whole columns per thread");
-        constexpr int CPR = NF / NTHR, NL = 2 * NSF;
-        // rows per load batch (the residual stencil loads 8 values per cell:
-        // two rows keep its registers within four waves per SIMD)
-        constexpr bool RES = PRO == PRO_RESID || PRO == PRO_RESID_F;
-        constexpr int RB0 = (RES || (PRO == PRO_DIV && sizeof(TO) == 4)) ? 2 : 4;
-        constexpr int RB = (NL % RB0 == 0) ? RB0 : ((NL % 2 == 0) ? 2 : 1);
-        // each thread owns the adjacent columns (2q, 2q + 1), q = tid + c NTHR
-        constexpr int PPR = CPR / 2;
-        static_assert(CPR % 2 == 0, "column pairs");
-        PairNb cn[PPR];
-        int lp0[PPR], lp1[PPR];
-        // post-twiddles of the outputs this thread stores (m = i, i + 1),
-        // loaded before the field rows
-        // (unconditionally: the tables exist for both boundary kinds, and a
-        // periodic line ignores them)
+    double ss = 0.0, s1 = 0.0, s2 = 0.0;
+    const int total = nl * N;
+    constexpr int PER = 2 * EMAX / NTHR;   // elements per thread, >= total / NTHR
+    constexpr int BAT = (PER % 4 == 0) ? 4 : 1;
+    for (int r0 = 0; r0 < PER; r0 += BAT) {
+        TI val[BAT];
 #pragma unroll
-        for (int c = 0; c < PPR; ++c) {
-            const int i = 2 * (threadIdx.x + c * NTHR);
-            pw[c][0] = a.dctc[i];
-            pw[c][1] = a.dcts[i];
-            pw[c][2] = a.dctc[i + 1];
-            pw[c][3] = a.dcts[i + 1];
-        }
-#pragma unroll
-        for (int c = 0; c < PPR; ++c) {
-            const int i = 2 * (threadIdx.x + c * NTHR);
-            cn[c] = pair_nb(i, NF, a.bcx);
-            lp0[c] = li(0, (a.bcx == FSEI_BC_WALL) ? mk_pos(i, NF) : i, SP);
-            lp1[c] = li(0, (a.bcx == FSEI_BC_WALL) ? mk_pos(i + 1, NF) : i + 1, SP);
-        }
-        // residual prologue: the iterate's rows carried down the tile (rows
-        // l - 1 and l in registers, row l + 1 loaded; the tile's first and
-        // last rows take their outer neighbours from row_nb), so a row costs
-        // 6 loads instead of 8; same arithmetic as x_prologue_pair
-        double2 pprev[PPR], pcur[PPR];
-        typename Vec2T<TI>::type vcur[PPR];
-        if constexpr (PRO == PRO_DIV || PRO == PRO_DIV_ADJ) {
-#pragma unroll
-            for (int c = 0; c < PPR; ++c) vcur[c] = *reinterpret_cast<const typename Vec2T<TI>::type*>(a.v + base + cn[c].i);
-        }
-        if constexpr (RES) {
-            const auto* __restrict__ pp = resid_iterate<PRO>(a) + base;
-            const RowNb rn0 = row_nb(k0, j0, NF, a.ny, a.nz, a.bcy);
-#pragma unroll
-            for (int c = 0; c < PPR; ++c) {
-                pcur[c] = pair_d(pp + cn[c].i);
-                pprev[c] = pair_d(pp + rn0.ym + (long)cn[c].i);
-            }
-        }
-#pragma unroll
-        for (int l0 = 0; l0 < NL; l0 += RB) {
-            TI val0[RB][PPR], val1[RB][PPR];
-            if constexpr (RES) {
-                // the host launches this path only when ny is a multiple of
-                // the rows per tile, so all rows of a tile share plane k0
-                const auto* __restrict__ pp = resid_iterate<PRO>(a) + base;
-                double2 pn[RB][PPR], pzp[RB][PPR], pzm[RB][PPR], fc[RB][PPR];
-                double pxm[RB][PPR], pxp[RB][PPR];
-#pragma unroll
-                for (int lr = 0; lr < RB; ++lr) {
-                    const int l = l0 + lr;
-                    const RowNb rn = row_nb(k0, j0 + l, NF, a.ny, a.nz, a.bcy);
-                    const long ynext = (l + 1 < NL) ? (long)NF : rn.yp;
-#pragma unroll
-                    for (int c = 0; c < PPR; ++c) {
-                        const long ro = (long)l * NF + cn[c].i;
-                        pn[lr][c] = pair_d(pp + ro + ynext);
-                        pzp[lr][c] = pair_d(pp + ro + rn.zp);
-                        pzm[lr][c] = pair_d(pp + ro + rn.zm);
-                        fc[lr][c] = *reinterpret_cast<const double2*>(a.f + base + ro);
-                        pxm[lr][c] = (double)pp[(long)l * NF + cn[c].im];
-                        pxp[lr][c] = (double)pp[(long)l * NF + cn[c].ip2];
-                    }
-                }
-                const double zc = a.zc[k0], za = a.za[k0], mean = a.scal[0];
-#pragma unroll
-                for (int lr = 0; lr < RB; ++lr) {
-                    const int l = l0 + lr;
-                    const RowNb rn = row_nb(k0, j0 + l, NF, a.ny, a.nz, a.bcy);
-#pragma unroll
-                    for (int c = 0; c < PPR; ++c) {
-                        const double2 pc = pcur[c], pym = pprev[c], pyp = pn[lr][c];
-                        const double lx0 = (pc.y - pc.x) + (cn[c].him ? pxm[lr][c] - pc.x : 0.0);
-                        const double lx1 = (cn[c].hip2 ? pxp[lr][c] - pc.y : 0.0) + (pc.x - pc.y);
-                        const double ly0 = (rn.hyp ? pyp.x - pc.x : 0.0) + (rn.hym ? pym.x - pc.x : 0.0);
-                        const double ly1 = (rn.hyp ? pyp.y - pc.y : 0.0) + (rn.hym ? pym.y - pc.y : 0.0);
-                        const double lz0 = (rn.hzp ? zc * (pzp[lr][c].x - pc.x) : 0.0) +
-                                           (rn.hzm ? za * (pzm[lr][c].x - pc.x) : 0.0);
-                        const double lz1 = (rn.hzp ? zc * (pzp[lr][c].y - pc.y) : 0.0) +
-                                           (rn.hzm ? za * (pzm[lr][c].y - pc.y) : 0.0);
-                        val0[lr][c] = (TI)((fc[lr][c].x - mean) - (lx0 * a.idx2 + ly0 * a.idy2 + lz0));
-                        val1[lr][c] = (TI)((fc[lr][c].y - mean) - (lx1 * a.idx2 + ly1 * a.idy2 + lz1));
-                        sp += pc.x + pc.y;
-                        pprev[c] = pc;
-                        pcur[c] = pyp;
-                    }
-                }
-            } else if constexpr (PRO == PRO_DIV || PRO == PRO_DIV_ADJ) {
-                // divergence: v carried down the tile like the residual's
-                // iterate (row l + 1 of v is row l's y+1 face), 5 loads per row
-                using V = typename Vec2T<TI>::type;
-                V uc[RB][PPR], vn[RB][PPR], wc[RB][PPR], wh[RB][PPR], gv[RB][PPR];
-                TI uh[RB][PPR];
-#pragma unroll
-                for (int lr = 0; lr < RB; ++lr) {
-                    const int l = l0 + lr;
-                    const RowNb rn = row_nb(k0, j0 + l, NF, a.ny, a.nz, a.bcy);
-                    const long ynext = (l + 1 < NL) ? (long)NF : rn.yp;
-#pragma unroll
-                    for (int c = 0; c < PPR; ++c) {
-                        const size_t ro = base + (size_t)l * NF;
-                        uc[lr][c] = *reinterpret_cast<const V*>(a.u + ro + cn[c].i);
-                        uh[lr][c] = a.u[ro + cn[c].ip2];
-                        vn[lr][c] = *reinterpret_cast<const V*>(a.v + (long)(ro + cn[c].i) + ynext);
-                        wc[lr][c] = *reinterpret_cast<const V*>(a.w + ro + cn[c].i);
-                        wh[lr][c] = *reinterpret_cast<const V*>(a.w + (long)(ro + cn[c].i) + rn.zp);
-                        if constexpr (PRO == PRO_DIV_ADJ) {
-                            if (a.gp) gv[lr][c] = *reinterpret_cast<const V*>(a.gp + ro + cn[c].i);
-                        }
-                    }
-                }
-                const TI zk = a.zeta[k0], ek = a.eta[k0], zero = (TI)0;
-#pragma unroll
-                for (int lr = 0; lr < RB; ++lr) {
-                    const int l = l0 + lr;
-                    const RowNb rn = row_nb(k0, j0 + l, NF, a.ny, a.nz, a.bcy);
-#pragma unroll
-                    for (int c = 0; c < PPR; ++c) {
-                        const V vc = vcur[c], vh = vn[lr][c];
-                        TI r0 = (uc[lr][c].y - (cn[c].him ? uc[lr][c].x : zero)) * a.idx +
-                                ((rn.hyp ? vh.x : zero) - (rn.hym ? vc.x : zero)) * a.idy +
-                                (zk * (rn.hzp ? wh[lr][c].x : zero) - ek * (rn.hzm ? wc[lr][c].x : zero));
-                        TI r1 = ((cn[c].hip2 ? uh[lr][c] : zero) - uc[lr][c].y) * a.idx +
-                                ((rn.hyp ? vh.y : zero) - (rn.hym ? vc.y : zero)) * a.idy +
-                                (zk * (rn.hzp ? wh[lr][c].y : zero) - ek * (rn.hzm ? wc[lr][c].y : zero));
-                        r0 *= a.alpha;
-                        r1 *= a.alpha;
-                        if constexpr (PRO == PRO_DIV_ADJ) {
-                            if (a.gp) {
-                                r0 += a.beta * gv[lr][c].x;
-                                r1 += a.beta * gv[lr][c].y;
-                            }
-                        }
-                        val0[lr][c] = r0;
-                        val1[lr][c] = r1;
-                        vcur[c] = vh;
-                    }
-                }
-            } else {
-#pragma unroll
-                for (int lr = 0; lr < RB; ++lr) {
-                    const int l = l0 + lr;
-                    const RowNb rn = row_nb(k0, j0 + l, NF, a.ny, a.nz, a.bcy);
-#pragma unroll
-                    for (int c = 0; c < PPR; ++c)
-                        x_prologue_pair<TI, TO, PRO>(a, base + (size_t)l * NF, k0, rn, cn[c], val0[lr][c],
-                                                     val1[lr][c]);
-                }
-            }
-            if (l0 == 0) twr.store(twl);
-#pragma unroll
-            for (int lr = 0; lr < RB; ++lr) {
-                const int l = l0 + lr;
-#pragma unroll
-                for (int c = 0; c < PPR; ++c) {
-                    const double v0 = (double)val0[lr][c], v1 = (double)val1[lr][c];
-                    if (out_f) *reinterpret_cast<double2*>(out_f + base + (size_t)l * NF + cn[c].i) = make_double2(v0, v1);
-                    ss += v0 * v0 + v1 * v1;
-                    s1 += v0 + v1;
-                    TO* dst = (l & 1) ? sim : sre;
-                    dst[(l >> 1) * SP + lp0[c]] = (TO)val0[lr][c];
-                    dst[(l >> 1) * SP + lp1[c]] = (TO)val1[lr][c];
+        for (int r = 0; r < BAT; ++r) {
+            const int e = threadIdx.x + (r0 + r) * NTHR;
+            val[r] = (TI)0;
+            if (e < total) {
+                const int l = e / N;
+                const int i = e - l * N;
+                if (row0 + l < nrows) {
+                    int k, j;
+                    row_kj(k0, j0, l, a.ny, k, j);
+                    val[r] = x_prologue<TI, TO, PRO>(a, base, k, j, i, e, N);
                 }
             }
         }
-        if (a.dzw) s2 = a.dzw[k0] * (RES ? sp : s1);   // every row of the tile is in plane k0
-    } else {
-        const int total = nl * N;
-        constexpr int PER = 2 * EMAX / NTHR;   // elements per thread, >= total / NTHR
-        constexpr int BAT = (PER % 4 == 0) ? 4 : 1;
-        for (int r0 = 0; r0 < PER; r0 += BAT) {
-            TI val[BAT];
 #pragma unroll
-            for (int r = 0; r < BAT; ++r) {
-                const int e = threadIdx.x + (r0 + r) * NTHR;
-                val[r] = (TI)0;
-                if (e < total) {
-                    const int l = e / N;
-                    const int i = e - l * N;
-                    if (row0 + l < nrows) {
+        for (int r = 0; r < BAT; ++r) {
+            const int e = threadIdx.x + (r0 + r) * NTHR;
+            if (e < total) {
+                const int l = e / N;
+                const int i = e - l * N;
+                if (row0 + l < nrows) {
+                    if (out_f) out_f[base + e] = (double)val[r];
+                    ss += (double)val[r] * (double)val[r];
+                    s1 += (double)val[r];
+                    if (a.dzw) {
                         int k, j;
                         row_kj(k0, j0, l, a.ny, k, j);
-                        val[r] = x_prologue<TI, TO, PRO>(a, base, k, j, i, e, N);
+                        constexpr bool RES = PRO == PRO_RESID || PRO == PRO_RESID_F;
+                        s2 += a.dzw[k] * (RES ? (double)resid_iterate<PRO>(a)[base + e] : (double)val[r]);
                     }
                 }
-            }
-#pragma unroll
-            for (int r = 0; r < BAT; ++r) {
-                const int e = threadIdx.x + (r0 + r) * NTHR;
-                if (e < total) {
-                    const int l = e / N;
-                    const int i = e - l * N;
-                    if (row0 + l < nrows) {
-                        if (out_f) out_f[base + e] = (double)val[r];
-                        ss += (double)val[r] * (double)val[r];
-                        s1 += (double)val[r];
-                        if (a.dzw) {
-                            int k, j;
-                            row_kj(k0, j0, l, a.ny, k, j);
-                            constexpr bool RES = PRO == PRO_RESID || PRO == PRO_RESID_F;
-                            s2 += a.dzw[k] * (RES ? (double)resid_iterate<PRO>(a)[base + e] : (double)val[r]);
-                        }
-                    }
-                    const int n = (a.bcx == FSEI_BC_WALL) ? mk_pos(i, N) : i;
-                    if (l & 1) sim[li(l >> 1, n, SP)] = (TO)val[r];
-                    else sre[li(l >> 1, n, SP)] = (TO)val[r];
-                }
+                const int n = (a.bcx == FSEI_BC_WALL) ? mk_pos(i, N) : i;
+                if (l & 1) sim[li(l >> 1, n, SP)] = (TO)val[r];
+                else sre[li(l >> 1, n, SP)] = (TO)val[r];
             }
         }
     }
@@ -738,43 +418,19 @@ __global__ __launch_bounds__(NTHR) void k_xfwd(XFwdArgs<TI, TO> a) {
         __syncthreads();
     }
     if (a.out == nullptr) return;   // norm-only pass (uniform over the block)
-    fft_lds<TO, EMAX, NTHR, -1, NF>(sre, sim, N, nseq, a.fp, twl, twl + N);
+    fft_lds<TO, EMAX, NTHR, -1>(sre, sim, N, nseq, a.fp, twl, twl + N);
     TO* __restrict__ out = a.out + base;
-    if constexpr (NF > 0) {
-        // outputs m, m + 1 (m even) of every line pair, stored as pairs
-        using VO = typename Vec2T<TO>::type;
-        constexpr int PPR = NF / NTHR / 2;
+    constexpr int PST = EMAX / NTHR;
 #pragma unroll
-        for (int c = 0; c < PPR; ++c) {
-            const int m0 = 2 * (threadIdx.x + c * NTHR), m1 = m0 + 1;
-            const int mm0 = (m0 == 0) ? 0 : NF - m0, mm1 = NF - m1;
-            const int l0 = li(0, m0, SP), lm0 = li(0, mm0, SP), l1 = li(0, m1, SP), lm1 = li(0, mm1, SP);
-            const bool lo0 = 2 * m0 <= NF, lo1 = 2 * m1 <= NF;
-            const TO wr0 = pw[c][0], wi0 = -pw[c][1], wr1 = pw[c][2], wi1 = -pw[c][3];
-#pragma unroll
-            for (int s = 0; s < NSF; ++s) {
-                VO xa, xb;
-                post_fwd_v<TO>(a.bcx, lo0, sre[s * SP + l0], sim[s * SP + l0], sre[s * SP + lm0], sim[s * SP + lm0],
-                               wr0, wi0, xa.x, xb.x);
-                post_fwd_v<TO>(a.bcx, lo1, sre[s * SP + l1], sim[s * SP + l1], sre[s * SP + lm1], sim[s * SP + lm1],
-                               wr1, wi1, xa.y, xb.y);
-                *reinterpret_cast<VO*>(out + (2 * s) * NF + m0) = xa;
-                *reinterpret_cast<VO*>(out + (2 * s + 1) * NF + m0) = xb;
-            }
-        }
-    } else {
-        constexpr int PST = EMAX / NTHR;
-#pragma unroll
-        for (int r = 0; r < PST; ++r) {
-            const int e = threadIdx.x + r * NTHR;
-            if (e < nseq * N) {
-                const int s = e / N;
-                const int m = e - s * N;
-                TO xa, xb;
-                post_fwd<TO>(sre, sim, s, SP, N, m, a.bcx, a.dctc, a.dcts, xa, xb);
-                if (row0 + 2 * s < nrows) out[2 * s * N + m] = xa;
-                if (row0 + 2 * s + 1 < nrows) out[(2 * s + 1) * N + m] = xb;
-            }
+    for (int r = 0; r < PST; ++r) {
+        const int e = threadIdx.x + r * NTHR;
+        if (e < nseq * N) {
+            const int s = e / N;
+            const int m = e - s * N;
+            TO xa, xb;
+            post_fwd<TO>(sre, sim, s, SP, N, m, a.bcx, a.dctc, a.dcts, xa, xb);
+            if (row0 + 2 * s < nrows) out[2 * s * N + m] = xa;
+            if (row0 + 2 * s + 1 < nrows) out[(2 * s + 1) * N + m] = xb;
         }
     }
 }
@@ -785,7 +441,7 @@ __global__ __launch_bounds__(NTHR) void k_xfwd(XFwdArgs<TI, TO> a) {
 // ---------------------------------------------------------------------------
 // STORE: out = result; ACC: out += result; ADDF: out = add32 + result;
 // ACC_KEEP: out += result and the result is also written back over the input
-enum { EPI_STORE = 0, EPI_ACC = 1, EPI_ADDF = 2, EPI_ACC_KEEP = 3 };
+enum { EPI_STORE = 0, EPI_ACC = 1, EPI_ADDF = 2, EPI_ACC_KEEP = 3, EPI_KINDS = 4 };
 
 template <typename T, typename TP>
 struct XInvArgs {
@@ -803,184 +459,62 @@ struct XInvArgs {
     const T* dcts;
 };
 
-template <typename T, typename TP, int EPI, int EMAX, int NTHR, int NF>
+template <typename T, typename TP, int EPI, int EMAX, int NTHR>
 __global__ __launch_bounds__(NTHR) void k_xinv(XInvArgs<T, TP> a) {
     __shared__ T sre[lds_elems(EMAX)];
     __shared__ T sim[lds_elems(EMAX)];
-    constexpr int NSF = NF > 0 ? tile_nseq(EMAX, NF) : 0;
-    const int N = NF > 0 ? NF : a.nx;
+    const int N = a.nx;
     const int SP = seq_stride(N);
-    const int nseq = NF > 0 ? NSF : a.nseq;
+    const int nseq = a.nseq;
     const int nl = 2 * nseq;
     const long row0 = xcd_remap(blockIdx.x, gridDim.x) * nl;
     const long nrows = (long)a.ny * a.nz;
     const size_t base = (size_t)row0 * N;
     const T* in = a.in + base;   // not restrict: ACC_KEEP writes this field back (after every read of it)
-    T* twl = lds_twiddle_ptr<T>();
-    TwiddleRegs<T, NTHR, (NF > 0 ? NF : 1)> twr;
-    if constexpr (NF == 0) stage_twiddles<T, NTHR>(twl, a.twc, a.tws, N);
-    else twr.load(a.twc, a.tws);
-    if constexpr (NF > 0) {
-        static_assert(NF % NTHR == 0, "fixed x path: whole columns per thread");
-        constexpr int CPR = NF / NTHR;
-        static_assert(CPR % 2 == 0, "paired columns");
-        // each thread loads columns m < NF/2 and its partner NF - m once and
-        // forms both pre-twiddled values (m = 0 pairs with NF/2; both of
-        // those use only their own column)
+    T* twl = lds_twiddles<T, NTHR>(a.twc, a.tws, N);
+    constexpr int PLD = EMAX / NTHR;
 #pragma unroll
-        for (int c = 0; c < CPR / 2; ++c) {
-            const int m = threadIdx.x + c * NTHR;
-            const int nm = (m == 0) ? NF / 2 : NF - m;
-            const int lm = li(0, m, SP), lnm = li(0, nm, SP);
-            // pre-twiddles, loaded before the rows and unconditionally (a
-            // periodic line ignores them); cos/sin(pi m / 2NF) at NF - m
-            // are sin/cos at m
-            T cm = a.dctc[m], sm = a.dcts[m], c0 = a.dctc[NF / 2], s0 = a.dcts[NF / 2];
-            T xam[NSF], xanm[NSF], xbm[NSF], xbnm[NSF];
-#pragma unroll
-            for (int s = 0; s < NSF; ++s) {
-                xam[s] = in[(2 * s) * NF + m];
-                xanm[s] = in[(2 * s) * NF + nm];
-                xbm[s] = in[(2 * s + 1) * NF + m];
-                xbnm[s] = in[(2 * s + 1) * NF + nm];
+    for (int r = 0; r < PLD; ++r) {
+        const int e = threadIdx.x + r * NTHR;
+        if (e < nseq * N) {
+            const int s = e / N;
+            const int m = e - s * N;
+            const int nm = (m == 0) ? 0 : N - m;
+            T xam = 0, xanm = 0, xbm = 0, xbnm = 0;
+            if (row0 + 2 * s < nrows) {
+                xam = in[2 * s * N + m];
+                xanm = in[2 * s * N + nm];
             }
-            // (not used before the rows are requested)
-            asm volatile("" : "+v"(cm), "+v"(sm), "+v"(c0), "+v"(s0));
-            const T cn = (m == 0) ? c0 : sm, sn = (m == 0) ? s0 : cm;
-            if (c == 0) twr.store(twl);
-#pragma unroll
-            for (int s = 0; s < NSF; ++s) {
-                const T pa = (m == 0) ? xanm[s] : xam[s], pb = (m == 0) ? xbnm[s] : xbm[s];
-                T zr, zi;
-                pre_inv_cs<T>(NF, m, a.bcx, xam[s], xanm[s], xbm[s], xbnm[s], cm, sm, zr, zi);
-                sre[s * SP + lm] = zr;
-                sim[s * SP + lm] = zi;
-                pre_inv_cs<T>(NF, nm, a.bcx, xanm[s], pa, xbnm[s], pb, cn, sn, zr, zi);
-                sre[s * SP + lnm] = zr;
-                sim[s * SP + lnm] = zi;
+            if (row0 + 2 * s + 1 < nrows) {
+                xbm = in[(2 * s + 1) * N + m];
+                xbnm = in[(2 * s + 1) * N + nm];
             }
-        }
-    } else {
-        constexpr int PLD = EMAX / NTHR;
-#pragma unroll
-        for (int r = 0; r < PLD; ++r) {
-            const int e = threadIdx.x + r * NTHR;
-            if (e < nseq * N) {
-                const int s = e / N;
-                const int m = e - s * N;
-                const int nm = (m == 0) ? 0 : N - m;
-                T xam = 0, xanm = 0, xbm = 0, xbnm = 0;
-                if (row0 + 2 * s < nrows) {
-                    xam = in[2 * s * N + m];
-                    xanm = in[2 * s * N + nm];
-                }
-                if (row0 + 2 * s + 1 < nrows) {
-                    xbm = in[(2 * s + 1) * N + m];
-                    xbnm = in[(2 * s + 1) * N + nm];
-                }
-                T zr, zi;
-                pre_inv<T>(N, m, a.bcx, xam, xanm, xbm, xbnm, a.dctc, a.dcts, zr, zi);
-                sre[li(s, m, SP)] = zr;
-                sim[li(s, m, SP)] = zi;
-            }
+            T zr, zi;
+            pre_inv<T>(N, m, a.bcx, xam, xanm, xbm, xbnm, a.dctc, a.dcts, zr, zi);
+            sre[li(s, m, SP)] = zr;
+            sim[li(s, m, SP)] = zi;
         }
     }
     TP* __restrict__ out = a.out + base;
-    // fixed path, accumulating epilogues: the values the result is added to
-    // (the iterate, or the FP32 field) are loaded before the transform and
-    // arrive while it runs
-    constexpr bool ACCF = NF > 0 && (EPI == EPI_ACC || EPI == EPI_ADDF || EPI == EPI_ACC_KEEP);
-    constexpr int NLA = ACCF ? 2 * NSF : 1, PPA = ACCF ? NF / NTHR / 2 : 1;
-    using VPA = typename Vec2T<TP>::type;
-    VPA old[NLA][PPA];
-    if constexpr (ACCF) {
-        const float* __restrict__ add = (EPI == EPI_ADDF) ? a.add32 + base : nullptr;
-#pragma unroll
-        for (int l = 0; l < NLA; ++l)
-#pragma unroll
-            for (int c = 0; c < PPA; ++c) {
-                const int o = l * NF + 2 * (threadIdx.x + c * NTHR);
-                if constexpr (EPI == EPI_ADDF) {
-                    const float2 q = *reinterpret_cast<const float2*>(add + o);
-                    old[l][c].x = (TP)q.x;
-                    old[l][c].y = (TP)q.y;
-                } else {
-                    old[l][c] = *reinterpret_cast<const VPA*>(out + o);
-                }
-            }
-    }
     __syncthreads();
-    fft_lds<T, EMAX, NTHR, 1, NF>(sre, sim, N, nseq, a.fp, twl, twl + N);
-    if constexpr (NF > 0) {
-        // outputs i, i + 1 (i even) of every line, read and written as pairs
-        using VT = typename Vec2T<T>::type;
-        using VP = typename Vec2T<TP>::type;
-        constexpr int PPR = NF / NTHR / 2, NL = 2 * NSF;
-        static_assert(NF % (2 * NTHR) == 0, "column pairs");
-        int ln0[PPR], ln1[PPR];
+    fft_lds<T, EMAX, NTHR, 1>(sre, sim, N, nseq, a.fp, twl, twl + N);
+    constexpr int PST = 2 * EMAX / NTHR;
+    const TP msub = (EPI != EPI_STORE && a.vsum) ? (TP)(a.vsum[0] * a.vscale) : (TP)0;
 #pragma unroll
-        for (int c = 0; c < PPR; ++c) {
-            const int i = 2 * (threadIdx.x + c * NTHR);
-            ln0[c] = li(0, (a.bcx == FSEI_BC_WALL) ? mk_pos(i, NF) : i, SP);
-            ln1[c] = li(0, (a.bcx == FSEI_BC_WALL) ? mk_pos(i + 1, NF) : i + 1, SP);
-        }
-        if constexpr (ACCF) {
-            static_assert(NLA == NL && PPA == PPR, "prefetched epilogue values");
-            const TP msub = a.vsum ? (TP)(a.vsum[0] * a.vscale) : (TP)0;
-#pragma unroll
-            for (int l = 0; l < NL; ++l)
-#pragma unroll
-                for (int c = 0; c < PPR; ++c) {
-                    old[l][c].x -= msub;
-                    old[l][c].y -= msub;
-                }
-#pragma unroll
-            for (int l = 0; l < NL; ++l)
-#pragma unroll
-                for (int c = 0; c < PPR; ++c) {
-                    const int o = l * NF + 2 * (threadIdx.x + c * NTHR);
-                    const T* src = (l & 1) ? sim : sre;
-                    VT val;
-                    val.x = src[(l >> 1) * SP + ln0[c]];
-                    val.y = src[(l >> 1) * SP + ln1[c]];
-                    VP r;
-                    r.x = old[l][c].x + (TP)val.x;
-                    r.y = old[l][c].y + (TP)val.y;
-                    *reinterpret_cast<VP*>(out + o) = r;
-                    if constexpr (EPI == EPI_ACC_KEEP) *reinterpret_cast<VT*>(a.keep + base + o) = val;
-                }
-        } else {
-#pragma unroll
-            for (int l = 0; l < NL; ++l)
-#pragma unroll
-                for (int c = 0; c < PPR; ++c) {
-                    const int o = l * NF + 2 * (threadIdx.x + c * NTHR);
-                    const T* src = (l & 1) ? sim : sre;
-                    VP r;
-                    r.x = (TP)src[(l >> 1) * SP + ln0[c]];
-                    r.y = (TP)src[(l >> 1) * SP + ln1[c]];
-                    *reinterpret_cast<VP*>(out + o) = r;
-                }
-        }
-    } else {
-        constexpr int PST = 2 * EMAX / NTHR;
-        const TP msub = (EPI != EPI_STORE && a.vsum) ? (TP)(a.vsum[0] * a.vscale) : (TP)0;
-#pragma unroll
-        for (int r = 0; r < PST; ++r) {
-            const int e = threadIdx.x + r * NTHR;
-            if (e < nl * N) {
-                const int l = e / N;
-                const int i = e - l * N;
-                if (row0 + l < nrows) {
-                    const int n = (a.bcx == FSEI_BC_WALL) ? mk_pos(i, N) : i;
-                    const T val = (l & 1) ? sim[li(l >> 1, n, SP)] : sre[li(l >> 1, n, SP)];
-                    if constexpr (EPI == EPI_ACC) out[e] = (out[e] - msub) + (TP)val;
-                    else if constexpr (EPI == EPI_ADDF) out[e] = ((TP)a.add32[base + e] - msub) + (TP)val;
-                    else if constexpr (EPI == EPI_ACC_KEEP) {
-                        out[e] = (out[e] - msub) + (TP)val;
-                        a.keep[base + e] = val;
-                    } else out[e] = (TP)val;
-                }
+    for (int r = 0; r < PST; ++r) {
+        const int e = threadIdx.x + r * NTHR;
+        if (e < nl * N) {
+            const int l = e / N;
+            const int i = e - l * N;
+            if (row0 + l < nrows) {
+                const int n = (a.bcx == FSEI_BC_WALL) ? mk_pos(i, N) : i;
+                const T val = (l & 1) ? sim[li(l >> 1, n, SP)] : sre[li(l >> 1, n, SP)];
+                if constexpr (EPI == EPI_ACC) out[e] = (out[e] - msub) + (TP)val;
+                else if constexpr (EPI == EPI_ADDF) out[e] = ((TP)a.add32[base + e] - msub) + (TP)val;
+                else if constexpr (EPI == EPI_ACC_KEEP) {
+                    out[e] = (out[e] - msub) + (TP)val;
+                    a.keep[base + e] = val;
+                } else out[e] = (TP)val;
             }
         }
     }
@@ -1116,7 +650,7 @@ __global__ __launch_bounds__(xg_threads<NF>()) void k_xinv_grad(XInvGradArgs a) 
             sim[s * SP + lnm] = zi;
         }
         __syncthreads();
-        fft_lds<double, EMAX, NTHR, 1, NF>(sre, sim, NF, NSQ, FftPlan{}, twl, twl + NF);
+        fft_fixed<double, EMAX, NTHR, 1, NF, 0, 1>(sre, sim, NSQ, twl, twl + NF);
         // the next step's input is in flight during this step's gradient
         double2 pym = make_double2(pv(0, q0), pv(0, q1));
         if (!colt) {
@@ -1311,7 +845,7 @@ __global__ __launch_bounds__(xgr_threads<NF>()) void k_xinv_grad_resid(XInvGradR
             sim[s * SP + lnm] = zi;
         }
         __syncthreads();
-        fft_lds<float, EMAX, NTHR, 1, NF>(sre, sim, NF, NSQ, FftPlan{}, twl, twl + NF);
+        fft_fixed<float, EMAX, NTHR, 1, NF, 0, 1>(sre, sim, NSQ, twl, twl + NF);
         // uniform over the workgroup: this plane's own rows get the gradient
         // (grad), complete the residual of the plane below (lag), or only
         // provide p for the next plane (the chunk's halo plane)
@@ -1430,250 +964,110 @@ struct YArgs {
     const T* dcts;
 };
 
-template <typename T, int EMAX, int NTHR, int NF, int PS = kPadShift>
+template <typename T, int EMAX, int NTHR>
 __global__ __launch_bounds__(NTHR) void k_yfwd(YArgs<T> a) {
-    __shared__ T sre[lds_elems(EMAX, PS)];
-    __shared__ T sim[lds_elems(EMAX, PS)];
-    constexpr int NSF = NF > 0 ? tile_nseq(EMAX, NF, PS) : 0;
-    const int N = NF > 0 ? NF : a.ny;
-    const int SP = seq_stride(N, PS);
+    __shared__ T sre[lds_elems(EMAX)];
+    __shared__ T sim[lds_elems(EMAX)];
+    const int N = a.ny;
+    const int SP = seq_stride(N);
     const int nx = a.nx;
-    const int nseq = NF > 0 ? NSF : a.nseq;
+    const int nseq = a.nseq;
     const int TX = 2 * nseq;
-    // tiles in XCD-contiguous runs (measured: 8-20 % faster at 512 and 768;
-    // with 64-byte tile rows the two tiles sharing each 128-byte line also
-    // meet in one L2)
+    // tiles in XCD-contiguous runs: neighbouring tiles share an L2
     const int bx = (int)xcd_remap(blockIdx.x, gridDim.x);
     const int k = bx / a.ntile;
     const int tile = bx - k * a.ntile;
     const int i0 = tile * TX;
     T* __restrict__ d = a.data + (size_t)k * nx * N + i0;
-    // Fixed path: the post-twiddles cos, sin (pi m / 2NF) of the output rows
-    // are read before the tile, unconditionally (the tables exist for both
-    // boundary kinds; a periodic line ignores them): a table load between
-    // the stores would make every store wait for the previous one.  FP64
-    // keeps them in registers and its FFT twiddles' round trip overlaps the
-    // tile loads; FP32 tiles, whose second workgroup per CU allows no extra
-    // registers (1024 threads, at most 64 VGPRs), stage both tables in LDS
-    // first (post-twiddles at 2 NF and 3 NF; the launcher sizes the dynamic
-    // LDS).
-    constexpr bool TL = NF > 0 && sizeof(T) == 4;
-    T* twl = lds_twiddle_ptr<T>();
-    TwiddleRegs<T, NTHR, ((NF > 0 && !TL) ? NF : 1)> twr;
-    if constexpr (NF == 0 || TL) stage_twiddles<T, NTHR>(twl, a.twc, a.tws, N);
-    if constexpr (TL) stage_twiddles<T, NTHR>(twl + 2 * NF, a.dctc, a.dcts, NF);
-    if constexpr (NF > 0 && !TL) twr.load(a.twc, a.tws);
-    constexpr int YP = (NF > 0 && !TL) ? NF / (NTHR / (NSF > 0 ? NSF : 1)) : 1;
-    T wr[YP], wi[YP];
-    if constexpr (NF > 0) {
-        // lane: column pair s (= sequence s), rows jr + r * RPP
-        using V2 = typename Vec2T<T>::type;
-        constexpr int RPP = NTHR / NSF, NPASS = NF / RPP;
-        static_assert(NTHR % NSF == 0 && NF % RPP == 0 && RPP % 2 == 0, "fixed y tile");
-        const int s = threadIdx.x % NSF, jr = threadIdx.x / NSF;
-        const unsigned lo = (unsigned)(jr * nx + 2 * s);
-        if constexpr (!TL) {
+    T* twl = lds_twiddles<T, NTHR>(a.twc, a.tws, N);
+    constexpr int PLD = 2 * EMAX / NTHR;
+    T val[PLD];
 #pragma unroll
-            for (int r = 0; r < NPASS; ++r) {
-                const int m = jr + r * RPP;
-                wr[r] = a.dctc[m];
-                wi[r] = a.dcts[m];
-            }
-        }
-        V2 val[NPASS];
+    for (int r = 0; r < PLD; ++r) {
+        const int e = threadIdx.x + r * NTHR;
+        const int j = e / TX;
+        const int c = e - j * TX;
+        val[r] = (e < TX * N && i0 + c < nx) ? d[j * nx + c] : (T)0;
+    }
 #pragma unroll
-        for (int r = 0; r < NPASS; ++r) val[r] = *reinterpret_cast<const V2*>(d + (size_t)(r * RPP) * nx + lo);
-        // keep the post-twiddles in registers from here on (the compiler
-        // would otherwise reload each next to its use, one wait per row)
-        if constexpr (!TL) {
-#pragma unroll
-            for (int r = 0; r < NPASS; ++r) asm volatile("" : "+v"(wr[r]), "+v"(wi[r]));
-            twr.store(twl);
-        }
-#pragma unroll
-        for (int r = 0; r < NPASS; ++r) {
-            const int j = jr + r * RPP;
-            const int o = s * SP + li<PS>(0, (a.bcy == FSEI_BC_WALL) ? mk_pos(j, NF) : j, SP);
-            sre[o] = val[r].x;
-            sim[o] = val[r].y;
-        }
-    } else {
-        constexpr int PLD = 2 * EMAX / NTHR;
-        T val[PLD];
-#pragma unroll
-        for (int r = 0; r < PLD; ++r) {
-            const int e = threadIdx.x + r * NTHR;
+    for (int r = 0; r < PLD; ++r) {
+        const int e = threadIdx.x + r * NTHR;
+        if (e < TX * N) {
             const int j = e / TX;
             const int c = e - j * TX;
-            val[r] = (e < TX * N && i0 + c < nx) ? d[j * nx + c] : (T)0;
-        }
-#pragma unroll
-        for (int r = 0; r < PLD; ++r) {
-            const int e = threadIdx.x + r * NTHR;
-            if (e < TX * N) {
-                const int j = e / TX;
-                const int c = e - j * TX;
-                const int n = (a.bcy == FSEI_BC_WALL) ? mk_pos(j, N) : j;
-                if (c & 1) sim[li<PS>(c >> 1, n, SP)] = val[r];
-                else sre[li<PS>(c >> 1, n, SP)] = val[r];
-            }
+            const int n = (a.bcy == FSEI_BC_WALL) ? mk_pos(j, N) : j;
+            if (c & 1) sim[li(c >> 1, n, SP)] = val[r];
+            else sre[li(c >> 1, n, SP)] = val[r];
         }
     }
     __syncthreads();
-    fft_lds<T, EMAX, NTHR, -1, NF, PS>(sre, sim, N, nseq, a.fp, twl, twl + N);
-    if constexpr (NF > 0) {
-        using V2 = typename Vec2T<T>::type;
-        constexpr int RPP = NTHR / NSF, NPASS = NF / RPP;
-        const int s = threadIdx.x % NSF, mr = threadIdx.x / NSF;
-        const unsigned lo = (unsigned)(mr * nx + 2 * s);
+    fft_lds<T, EMAX, NTHR, -1>(sre, sim, N, nseq, a.fp, twl, twl + N);
+    constexpr int PST = EMAX / NTHR;
 #pragma unroll
-        for (int r = 0; r < NPASS; ++r) {
-            const int m = mr + r * RPP;
-            const int mm = (m == 0) ? 0 : NF - m;
-            const int om = s * SP + li<PS>(0, m, SP), omm = s * SP + li<PS>(0, mm, SP);
-            V2 res;
-            const T cr = TL ? twl[2 * NF + m] : wr[TL ? 0 : r];
-            const T sr = TL ? twl[3 * NF + m] : wi[TL ? 0 : r];
-            post_fwd_v<T>(a.bcy, 2 * m <= NF, sre[om], sim[om], sre[omm], sim[omm], cr, -sr, res.x, res.y);
-            *reinterpret_cast<V2*>(d + (size_t)(r * RPP) * nx + lo) = res;
-        }
-    } else {
-        constexpr int PST = EMAX / NTHR;
-#pragma unroll
-        for (int r = 0; r < PST; ++r) {
-            const int e = threadIdx.x + r * NTHR;
-            if (e < nseq * N) {
-                const int m = e / nseq;
-                const int s = e - m * nseq;
-                T xa, xb;
-                post_fwd<T, PS>(sre, sim, s, SP, N, m, a.bcy, a.dctc, a.dcts, xa, xb);
-                if (i0 + 2 * s < nx) d[m * nx + 2 * s] = xa;
-                if (i0 + 2 * s + 1 < nx) d[m * nx + 2 * s + 1] = xb;
-            }
+    for (int r = 0; r < PST; ++r) {
+        const int e = threadIdx.x + r * NTHR;
+        if (e < nseq * N) {
+            const int m = e / nseq;
+            const int s = e - m * nseq;
+            T xa, xb;
+            post_fwd<T>(sre, sim, s, SP, N, m, a.bcy, a.dctc, a.dcts, xa, xb);
+            if (i0 + 2 * s < nx) d[m * nx + 2 * s] = xa;
+            if (i0 + 2 * s + 1 < nx) d[m * nx + 2 * s + 1] = xb;
         }
     }
 }
 
-template <typename T, int EMAX, int NTHR, int NF, int PS = kPadShift>
+template <typename T, int EMAX, int NTHR>
 __global__ __launch_bounds__(NTHR) void k_yinv(YArgs<T> a) {
-    __shared__ T sre[lds_elems(EMAX, PS)];
-    __shared__ T sim[lds_elems(EMAX, PS)];
-    constexpr int NSF = NF > 0 ? tile_nseq(EMAX, NF, PS) : 0;
-    const int N = NF > 0 ? NF : a.ny;
-    const int SP = seq_stride(N, PS);
+    __shared__ T sre[lds_elems(EMAX)];
+    __shared__ T sim[lds_elems(EMAX)];
+    const int N = a.ny;
+    const int SP = seq_stride(N);
     const int nx = a.nx;
-    const int nseq = NF > 0 ? NSF : a.nseq;
+    const int nseq = a.nseq;
     const int TX = 2 * nseq;
-    // tiles in XCD-contiguous runs (measured: 8-20 % faster at 512 and 768;
-    // with 64-byte tile rows the two tiles sharing each 128-byte line also
-    // meet in one L2)
+    // tiles in XCD-contiguous runs: neighbouring tiles share an L2
     const int bx = (int)xcd_remap(blockIdx.x, gridDim.x);
     const int k = bx / a.ntile;
     const int tile = bx - k * a.ntile;
     const int i0 = tile * TX;
     T* __restrict__ d = a.data + (size_t)k * nx * N + i0;
-    T* twl = lds_twiddle_ptr<T>();
-    TwiddleRegs<T, NTHR, (NF > 0 ? NF : 1)> twr;
-    if constexpr (NF == 0) stage_twiddles<T, NTHR>(twl, a.twc, a.tws, N);
-    else twr.load(a.twc, a.tws);
-    if constexpr (NF > 0) {
-        using V2 = typename Vec2T<T>::type;
-        constexpr int RPP = NTHR / NSF, NPASS = NF / RPP;
-        static_assert(NTHR % NSF == 0 && NF % RPP == 0 && RPP % 2 == 0, "fixed y tile");
-        const int s = threadIdx.x % NSF, mr = threadIdx.x / NSF;
-        const unsigned lo = (unsigned)(2 * s);
-        // each lane loads rows m < NF/2 and its partner NF - m once and
-        // forms both pre-twiddled values (m = 0 pairs with NF/2; both
-        // of those use only their own row)
-        constexpr int NH = NPASS / 2;
-        static_assert(NPASS % 2 == 0, "paired rows");
-        // pre-twiddles cos/sin(pi m / 2NF) of rows m, loaded before the data
-        // and unconditionally (a periodic line ignores them; at NF - m they
-        // are sin/cos at m; m = 0 pairs with NF/2)
-        T c[NH], sn[NH];
+    T* twl = lds_twiddles<T, NTHR>(a.twc, a.tws, N);
+    constexpr int PLD = EMAX / NTHR;
 #pragma unroll
-        for (int r = 0; r < NH; ++r) {
-            const int m = mr + r * RPP;
-            c[r] = a.dctc[m];
-            sn[r] = a.dcts[m];
-        }
-        const T c0 = a.dctc[NF / 2], s0 = a.dcts[NF / 2];
-        V2 A[NH], B[NH];
-#pragma unroll
-        for (int r = 0; r < NH; ++r) {
-            const int m = mr + r * RPP;
-            const int nm = (m == 0) ? NF / 2 : NF - m;
-            A[r] = *reinterpret_cast<const V2*>(d + (size_t)m * nx + lo);
-            B[r] = *reinterpret_cast<const V2*>(d + (size_t)nm * nx + lo);
-        }
-        twr.store(twl);
-#pragma unroll
-        for (int r = 0; r < NH; ++r) {
-            const int m = mr + r * RPP;
-            const int nm = (m == 0) ? NF / 2 : NF - m;
-            const V2 Am = (m == 0) ? B[r] : A[r];
-            const T cp = (m == 0) ? c0 : sn[r], sp = (m == 0) ? s0 : c[r];
-            T zr, zi;
-            pre_inv_cs<T>(NF, m, a.bcy, A[r].x, B[r].x, A[r].y, B[r].y, c[r], sn[r], zr, zi);
-            sre[s * SP + li<PS>(0, m, SP)] = zr;
-            sim[s * SP + li<PS>(0, m, SP)] = zi;
-            pre_inv_cs<T>(NF, nm, a.bcy, B[r].x, Am.x, B[r].y, Am.y, cp, sp, zr, zi);
-            sre[s * SP + li<PS>(0, nm, SP)] = zr;
-            sim[s * SP + li<PS>(0, nm, SP)] = zi;
-        }
-    } else {
-        constexpr int PLD = EMAX / NTHR;
-#pragma unroll
-        for (int r = 0; r < PLD; ++r) {
-            const int e = threadIdx.x + r * NTHR;
-            if (e < nseq * N) {
-                const int m = e / nseq;
-                const int s = e - m * nseq;
-                const int nm = (m == 0) ? 0 : N - m;
-                T xam = 0, xanm = 0, xbm = 0, xbnm = 0;
-                if (i0 + 2 * s < nx) {
-                    xam = d[m * nx + 2 * s];
-                    xanm = d[nm * nx + 2 * s];
-                }
-                if (i0 + 2 * s + 1 < nx) {
-                    xbm = d[m * nx + 2 * s + 1];
-                    xbnm = d[nm * nx + 2 * s + 1];
-                }
-                T zr, zi;
-                pre_inv<T>(N, m, a.bcy, xam, xanm, xbm, xbnm, a.dctc, a.dcts, zr, zi);
-                sre[li<PS>(s, m, SP)] = zr;
-                sim[li<PS>(s, m, SP)] = zi;
+    for (int r = 0; r < PLD; ++r) {
+        const int e = threadIdx.x + r * NTHR;
+        if (e < nseq * N) {
+            const int m = e / nseq;
+            const int s = e - m * nseq;
+            const int nm = (m == 0) ? 0 : N - m;
+            T xam = 0, xanm = 0, xbm = 0, xbnm = 0;
+            if (i0 + 2 * s < nx) {
+                xam = d[m * nx + 2 * s];
+                xanm = d[nm * nx + 2 * s];
             }
+            if (i0 + 2 * s + 1 < nx) {
+                xbm = d[m * nx + 2 * s + 1];
+                xbnm = d[nm * nx + 2 * s + 1];
+            }
+            T zr, zi;
+            pre_inv<T>(N, m, a.bcy, xam, xanm, xbm, xbnm, a.dctc, a.dcts, zr, zi);
+            sre[li(s, m, SP)] = zr;
+            sim[li(s, m, SP)] = zi;
         }
     }
     __syncthreads();
-    fft_lds<T, EMAX, NTHR, 1, NF, PS>(sre, sim, N, nseq, a.fp, twl, twl + N);
-    if constexpr (NF > 0) {
-        using V2 = typename Vec2T<T>::type;
-        constexpr int RPP = NTHR / NSF, NPASS = NF / RPP;
-        const int s = threadIdx.x % NSF, jr = threadIdx.x / NSF;
-        const unsigned lo = (unsigned)(jr * nx + 2 * s);
+    fft_lds<T, EMAX, NTHR, 1>(sre, sim, N, nseq, a.fp, twl, twl + N);
+    constexpr int PST = 2 * EMAX / NTHR;
 #pragma unroll
-        for (int r = 0; r < NPASS; ++r) {
-            const int j = jr + r * RPP;
-            const int o = s * SP + li<PS>(0, (a.bcy == FSEI_BC_WALL) ? mk_pos(j, NF) : j, SP);
-            V2 res;
-            res.x = sre[o];
-            res.y = sim[o];
-            *reinterpret_cast<V2*>(d + (size_t)(r * RPP) * nx + lo) = res;
-        }
-    } else {
-        constexpr int PST = 2 * EMAX / NTHR;
-#pragma unroll
-        for (int r = 0; r < PST; ++r) {
-            const int e = threadIdx.x + r * NTHR;
-            if (e < TX * N) {
-                const int j = e / TX;
-                const int c = e - j * TX;
-                if (i0 + c < nx) {
-                    const int n = (a.bcy == FSEI_BC_WALL) ? mk_pos(j, N) : j;
-                    d[j * nx + c] = (c & 1) ? sim[li<PS>(c >> 1, n, SP)] : sre[li<PS>(c >> 1, n, SP)];
-                }
+    for (int r = 0; r < PST; ++r) {
+        const int e = threadIdx.x + r * NTHR;
+        if (e < TX * N) {
+            const int j = e / TX;
+            const int c = e - j * TX;
+            if (i0 + c < nx) {
+                const int n = (a.bcy == FSEI_BC_WALL) ? mk_pos(j, N) : j;
+                d[j * nx + c] = (c & 1) ? sim[li(c >> 1, n, SP)] : sre[li(c >> 1, n, SP)];
             }
         }
     }
