@@ -32,12 +32,8 @@
  * Execution: every call enqueues kernels on the plan's stream and returns
  * without waiting, except (a) when an fsei_info pointer is passed (the call
  * then waits for the stream to read back scalars) and (b) FP32_REFINE with
- * rtol > 0 (one scalar is read back per refinement iteration).  Inside the z
- * solve the plan forks to a side stream of its own (created on the current
- * device by fsei_plan_set_workspace, destroyed with the plan) and joins it
- * with events before the next step, so work stays ordered on the plan's
- * stream.  A plan is not thread-safe; calls that share a plan must be
- * serialised by the caller.
+ * rtol > 0 (one scalar is read back per refinement iteration).  A plan is not
+ * thread-safe; calls that share a plan must be serialised by the caller.
  *
  * Errors: arguments are checked before anything is launched; no C++
  * exception crosses this interface.  A failing HIP call is reported as

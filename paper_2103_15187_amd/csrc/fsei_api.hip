@@ -83,15 +83,13 @@ void harvest(fsei_plan* p) {
     ts.pending.clear();
 }
 
-// Brackets one launch with events when timing is on (on the stream the
-// launch goes to: the plan's, or its side stream).
+// Brackets one launch with events when timing is on.
 struct Timed {
     fsei_plan* p;
     int slot;
     hipStream_t st;
     hipEvent_t a = nullptr, b = nullptr;
-    Timed(fsei_plan* pl, int s, void* stream = nullptr)
-        : p(pl), slot(s), st((hipStream_t)(stream ? stream : pl->stream)) {
+    Timed(fsei_plan* pl, int s) : p(pl), slot(s), st((hipStream_t)pl->stream) {
         if (p->timing) {
             TimingState& ts = tstate(p);
             if (ts.pending.size() > 4096) harvest(p);
@@ -436,10 +434,37 @@ bool choose_chunks(int nz, int pmax, int* L, int* P) {
     return false;
 }
 
+template <typename TS, typename TC, int PS, int L>
+void launch_zspecial(fsei_plan* p, const ZArgs<TS, TC>& a) {
+    constexpr int LN = 512 / PS;
+    Timed t(p, K_ZLIST);
+    hipLaunchKernelGGL((k_zspecial<TS, TC, PS, L>), dim3(1u + (unsigned)((a.nlist + LN - 1) / LN)), dim3(512), 0, S(p),
+                       a);
+}
+
+// grid of a z solve: the groups of special lines, then gx tiles per row of
+// modes.  Groups that would take the tiles' launch more than one round of the
+// CUs go ahead in a launch of their own.
+template <int PMAX, int NT, typename TS, typename TC>
+dim3 z_grid(fsei_plan* p, ZArgs<TS, TC>* a, int gx) {
+    const int ln = zspec_threads<NT>() / zspec_chunks(PMAX, a->L);
+    a->gx = gx;
+    a->nspec = 1 + (a->nlist + ln - 1) / ln;
+    if (a->nspec > cus_of_current_device()) {
+        if (a->nz <= 256) launch_zspecial<TS, TC, 64, 4>(p, *a);
+        else if (a->nz <= 512) launch_zspecial<TS, TC, 64, 8>(p, *a);
+        else if (a->nz <= 1024) launch_zspecial<TS, TC, 64, 16>(p, *a);
+        else launch_zspecial<TS, TC, 128, 16>(p, *a);
+        a->nspec = 0;
+    }
+    return dim3((unsigned)a->nspec + (unsigned)gx * (unsigned)a->ny);
+}
+
 template <typename TS, typename TC, int TXL, int NT>
-void z_dispatch(fsei_plan* p, ZArgs<TS, TC> a, dim3 grid, int slot) {
+void z_dispatch(fsei_plan* p, ZArgs<TS, TC> a) {
     const size_t dyn = 0;
-    Timed t(p, slot);
+    const dim3 grid = z_grid<NT / TXL, NT>(p, &a, (p->nx + TXL - 1) / TXL);
+    Timed t(p, K_ZSOLVE);
     switch (a.L) {
         case 4: hipLaunchKernelGGL((k_zsolve<TS, TC, TXL, 4, NT>), grid, dim3(NT), dyn, S(p), a); break;
         case 8: hipLaunchKernelGGL((k_zsolve<TS, TC, TXL, 8, NT>), grid, dim3(NT), dyn, S(p), a); break;
@@ -451,7 +476,8 @@ void z_dispatch(fsei_plan* p, ZArgs<TS, TC> a, dim3 grid, int slot) {
 }
 
 template <typename TS, typename TC, int M, int TXLM, int NT>
-void zv_dispatch(fsei_plan* p, ZArgs<TS, TC> a, dim3 grid) {
+void zv_dispatch(fsei_plan* p, ZArgs<TS, TC> a) {
+    const dim3 grid = z_grid<NT / TXLM, NT>(p, &a, (p->nx / M + TXLM - 1) / TXLM);
     Timed t(p, K_ZSOLVE);
     switch (a.L) {
         case 4: hipLaunchKernelGGL((k_zsolvev<TS, TC, M, TXLM, 4, NT>), grid, dim3(NT), 0, S(p), a); break;
@@ -464,7 +490,7 @@ void zv_dispatch(fsei_plan* p, ZArgs<TS, TC> a, dim3 grid) {
 }
 
 template <typename TS, typename TC>
-ZArgs<TS, TC> zargs(const fsei_plan* p, TS* data, int transposed) {
+ZArgs<TS, TC> zargs(const fsei_plan* p, TS* data, int transposed, bool record_mean) {
     ZArgs<TS, TC> a{};
     a.nx = p->nx;
     a.ny = p->ny;
@@ -481,7 +507,17 @@ ZArgs<TS, TC> zargs(const fsei_plan* p, TS* data, int transposed) {
     a.lamy = tab<TC>(p, T_LAMY);
     a.lamx64 = tab<double>(p, T_LAMX);
     a.lamy64 = tab<double>(p, T_LAMY);
-    a.sigma_thr = 0.0;
+    a.sigma_thr = p->sigma_thr;   // the host's threshold, compared in FP64
+    a.nlist = p->nlist;
+    a.list = zlist(p);
+    a.scale64 = 1.0 / ((double)p->nx * (double)p->ny);
+    a.lz = p->lz;
+    a.za64 = tab<double>(p, T_ZA);
+    a.zc64 = tab<double>(p, T_ZC);
+    a.dz64 = tab<double>(p, T_DZ);
+    a.inv_dz64 = tab<double>(p, T_INV_DZ);
+    a.h64 = tab<double>(p, T_H);
+    a.scal = (record_mean && !transposed) ? scalars(p) : nullptr;
     return a;
 }
 
@@ -498,61 +534,49 @@ void launch_z(fsei_plan* p, TS* data, int transposed, bool record_mean) {
     int L = 0, P = 0;
     const bool c32 = choose_chunks(nz, 32, &L, &P);
     // The near-singular lines and the (0,0) line are disjoint from the lines
-    // of the tiled kernel: they run on the plan's side stream (when it has
-    // one), concurrently with it, joined before the next step.
-    hipStream_t side = p->side_stream ? (hipStream_t)p->side_stream : S(p);
-    if (p->side_stream) {
-        (void)hipEventRecord((hipEvent_t)p->ev_fork, S(p));
-        (void)hipStreamWaitEvent(side, (hipEvent_t)p->ev_fork, 0);
-    }
+    // of the tiles; the first workgroups of the same launch take them.
     if constexpr (!F32) {
-        ZArgs<double, double> a = zargs<double, double>(p, data, transposed);
-        a.sigma_thr = p->sigma_thr;   // the host's threshold, compared in FP64
+        ZArgs<double, double> a = zargs<double, double>(p, data, transposed, record_mean);
         if (!transposed && c32 && L == 24 && P == 32 && nz == L * P && p->nx % 32 == 0 && aligned16(data)) {
             // whole 32-mode tiles of 768 rows: the persistent kernel with the
             // next tile's first 12 rows of each chunk staged in LDS (0.84 -> 0.66
-            // ms at 512x512x768), one workgroup per CU.  With near-singular
-            // lines, 32 CUs are left to their kernel on the side stream: with
-            // 8 or 16 left it still waited for the whole z solve (0.09 ms in
-            // series); with 32 the z solve takes 0.70 ms and the lines run beside it
+            // ms at 512x512x768), one workgroup per CU
             a.L = L;
             a.P = P;
+            z_grid<32, 512>(p, &a, p->nx / 32);
             Timed t(p, K_ZSOLVE);
             const long ntiles = (long)(p->nx / 32) * p->ny;
             const int cus = cus_of_current_device();
-            const long want = p->nlist > 0 && cus > 64 ? cus - 32 : cus;
-            const unsigned g = (unsigned)(ntiles < want ? ntiles : want);
+            const unsigned g = (unsigned)(ntiles < cus ? ntiles : cus);
             hipLaunchKernelGGL((k_zsolvev_pf<double, double, 2, 16, 24, 512, 12>), dim3(g), dim3(512), 0, S(p), a);
         } else if (c32 && L <= 24 && p->nx % 2 == 0) {
             a.L = L;
             a.P = P;
-            zv_dispatch<double, double, 2, 16, 512>(p, a, dim3((p->nx / 2 + 15) / 16, p->ny));
+            zv_dispatch<double, double, 2, 16, 512>(p, a);
         } else if (c32) {
             a.L = L;
             a.P = P;
-            z_dispatch<double, double, 16, 512>(p, a, dim3((p->nx + 15) / 16, p->ny), K_ZSOLVE);
+            z_dispatch<double, double, 16, 512>(p, a);
         } else {
             choose_chunks(nz, 64, &L, &P);
             a.L = L;
             a.P = P;
-            z_dispatch<double, double, 8, 512>(p, a, dim3((p->nx + 7) / 8, p->ny), K_ZSOLVE);
+            z_dispatch<double, double, 8, 512>(p, a);
         }
     } else {
-        ZArgs<float, float> a = zargs<float, float>(p, data, transposed);
-        a.sigma_thr = p->sigma_thr;   // the host's threshold, compared in FP64
+        ZArgs<float, float> a = zargs<float, float>(p, data, transposed, record_mean);
         if (!transposed && c32 && L == 24 && P == 32 && nz == L * P && p->nx % 64 == 0 && aligned16(data)) {
             // whole 64-mode tiles (256-B rows) of 768 rows: the persistent
             // kernel, one workgroup per CU, the next tile's first 12 rows of each
             // chunk staged in LDS (0.39 -> 0.375 ms at 512x512x768 against the
-            // two-workgroup 128-B tiling below); CUs left to the near-singular
-            // lines as in FP64
+            // two-workgroup 128-B tiling below)
             a.L = L;
             a.P = P;
+            z_grid<32, 512>(p, &a, p->nx / 64);
             Timed t(p, K_ZSOLVE);
             const long ntiles = (long)(p->nx / 64) * p->ny;
             const int cus = cus_of_current_device();
-            const long want = p->nlist > 0 && cus > 64 ? cus - 32 : cus;
-            const unsigned g = (unsigned)(ntiles < want ? ntiles : want);
+            const unsigned g = (unsigned)(ntiles < cus ? ntiles : cus);
             hipLaunchKernelGGL((k_zsolvev_pf<float, float, 4, 16, 24, 512, 12>), dim3(g), dim3(512), 0, S(p), a);
         } else if (c32 && L <= 24 && p->nx % 4 == 0) {
             a.L = L;
@@ -561,64 +585,25 @@ void launch_z(fsei_plan* p, TS* data, int transposed, bool record_mean) {
             // per CU, one solving while the other loads (11 % faster than 16
             // lanes in 512 threads, one per CU, at 512 x 512 x 768; the FP64
             // kernel the other way round, 18 % slower)
-            zv_dispatch<float, float, 4, 8, 256>(p, a, dim3((p->nx / 4 + 7) / 8, p->ny));
+            zv_dispatch<float, float, 4, 8, 256>(p, a);
         } else if (c32 && L <= 24 && p->nx % 2 == 0) {
             a.L = L;
             a.P = P;
-            zv_dispatch<float, float, 2, 32, 1024>(p, a, dim3((p->nx / 2 + 31) / 32, p->ny));
+            zv_dispatch<float, float, 2, 32, 1024>(p, a);
         } else if (p->nx % 2 == 0 && choose_chunks(nz, 64, &L, &P)) {
             a.L = L;
             a.P = P;
-            zv_dispatch<float, float, 2, 16, 1024>(p, a, dim3((p->nx / 2 + 15) / 16, p->ny));
+            zv_dispatch<float, float, 2, 16, 1024>(p, a);
         } else if (c32) {
             a.L = L;
             a.P = P;
-            z_dispatch<float, float, 32, 1024>(p, a, dim3((p->nx + 31) / 32, p->ny), K_ZSOLVE);
+            z_dispatch<float, float, 32, 1024>(p, a);
         } else {
             choose_chunks(nz, 64, &L, &P);
             a.L = L;
             a.P = P;
-            z_dispatch<float, float, 16, 1024>(p, a, dim3((p->nx + 15) / 16, p->ny), K_ZSOLVE);
+            z_dispatch<float, float, 16, 1024>(p, a);
         }
-    }
-    if (p->nlist > 0) {
-        ZSeqArgs<TS> b{};
-        b.nx = p->nx;
-        b.nz = nz;
-        b.nlist = p->nlist;
-        b.transposed = transposed;
-        b.stride = (size_t)p->nx * p->ny;
-        b.data = data;
-        b.list = zlist(p);
-        b.ys = reinterpret_cast<double*>((char*)p->ws + p->ws_seq);
-        b.cps = b.ys + (size_t)p->nlist * nz;
-        b.za = tab<double>(p, T_ZA);
-        b.zc = tab<double>(p, T_ZC);
-        b.lamx = tab<double>(p, T_LAMX);
-        b.lamy = tab<double>(p, T_LAMY);
-        b.dz = tab<double>(p, T_DZ);
-        b.scale = 1.0 / ((double)p->nx * (double)p->ny);
-        Timed t(p, K_ZLIST, side);
-        hipLaunchKernelGGL((k_zline_seq<TS>), dim3((unsigned)((p->nlist + 63) / 64)), dim3(64), 0, side, b);
-    }
-    ZeroArgs<TS> z{};
-    z.nz = nz;
-    z.transposed = transposed;
-    z.stride = (size_t)p->nx * p->ny;
-    z.data = data;
-    z.scale = 1.0 / ((double)p->nx * (double)p->ny);
-    z.lz = p->lz;
-    z.dz = tab<double>(p, T_DZ);
-    z.inv_dz = tab<double>(p, T_INV_DZ);
-    z.h = tab<double>(p, T_H);
-    z.scal = record_mean ? scalars(p) : nullptr;
-    {
-        Timed t(p, K_PREP, side);
-        hipLaunchKernelGGL((k_zero_mode<TS>), dim3(1), dim3(256), 0, side, z);
-    }
-    if (p->side_stream) {
-        (void)hipEventRecord((hipEvent_t)p->ev_join, side);
-        (void)hipStreamWaitEvent(S(p), (hipEvent_t)p->ev_join, 0);
     }
 }
 
@@ -1144,11 +1129,6 @@ void fsei_poisson_plan_destroy(fsei_plan* p) {
         for (auto e : ts->free_ev) (void)hipEventDestroy(e);
         delete ts;
     }
-    if (p->side_stream) {
-        (void)hipStreamDestroy((hipStream_t)p->side_stream);
-        (void)hipEventDestroy((hipEvent_t)p->ev_fork);
-        (void)hipEventDestroy((hipEvent_t)p->ev_join);
-    }
     delete p;
 }
 
@@ -1171,24 +1151,6 @@ fsei_status fsei_plan_set_workspace(fsei_plan* p, void* dev, size_t bytes) {
     p->ws = dev;
     p->ws_bytes = bytes;
     for (double& b : p->visc_beta) b = 0.0;   // viscous tables live in the workspace: rebuild on next use
-    if (!p->side_stream) {
-        // side stream (default priority) and the fork / join events of the z
-        // solve; without them everything runs on the plan's stream
-        hipStream_t st = nullptr;
-        hipEvent_t e0 = nullptr, e1 = nullptr;
-        if (hipStreamCreateWithFlags(&st, hipStreamNonBlocking) == hipSuccess &&
-            hipEventCreateWithFlags(&e0, hipEventDisableTiming) == hipSuccess &&
-            hipEventCreateWithFlags(&e1, hipEventDisableTiming) == hipSuccess) {
-            p->side_stream = st;
-            p->ev_fork = e0;
-            p->ev_join = e1;
-        } else {
-            if (st) (void)hipStreamDestroy(st);
-            if (e0) (void)hipEventDestroy(e0);
-            if (e1) (void)hipEventDestroy(e1);
-            (void)hipGetLastError();
-        }
-    }
     return FSEI_OK;
 }
 

@@ -9,7 +9,7 @@
 //   k_yfwd   : per tile of x-columns of one z-plane, forward y transform
 //   k_zsolve : per (kx, ky) mode, the z tridiagonal, partitioned over the
 //              threads of a workgroup (no global scratch)
-//   k_zero_mode : the singular (0,0) mode by prefix sums
+//              the near-singular lines and the singular (0,0) mode in the same launch
 //   k_yinv, k_xinv : inverse transforms (x inverse writes or accumulates p)
 //   k_grad   : gradient correction of the three velocity components
 #pragma once
@@ -56,6 +56,7 @@ __device__ __forceinline__ float zrcp(float x) {
 template <typename TS, typename TC>
 struct ZArgs {
     int nx, ny, nz, L, P, transposed;
+    int gx;               // tiles per row of modes
     TS* data;
     TC scale;             // 1/(nx ny)
     // skip the lines with |lamx64 + lamy64| < sigma_thr, tested in FP64 on
@@ -71,13 +72,332 @@ struct ZArgs {
     const TC* inv_dz;
     const TC* lamx;
     const TC* lamy;
+    // the zero mode and the near-singular lines, in FP64: nspec groups, taken
+    // by the launch's first workgroups (group 0: the zero mode; group g: the
+    // lines list[(g - 1) LN ...))
+    int nspec, nlist;
+    const int* list;      // line indices qy * nx + qx, ascending
+    double scale64, lz;
+    const double* za64;
+    const double* zc64;
+    const double* dz64;
+    const double* inv_dz64;
+    const double* h64;
+    double* scal;         // scal[0] <- removed mean of the zero mode's right-hand side, or null
 };
+
+// ---------------------------------------------------------------------------
+// Near-singular mode lines: |lambda_x + lambda_y| below the plan's threshold
+// (condition 1 + 4 / (dz_min^2 |sigma|) above 1e4), in FP64 with the pivots in
+// row-sum form.  With zero-flux walls every row of L_z + sigma sums to sigma,
+// so the pivot d_k = b_k - a_k c_{k-1} / d_{k-1}, b_k = -(a_k + c_k) + sigma,
+// equals g_k - c_k with g_k = sigma - a_k g_{k-1} / d_{k-1}, g_0 = sigma: every term
+// has the sign of sigma, nothing cancels.  Forming b_k first rounds the small
+// sigma against a_k + c_k, which costs up to ~1e-11 relative error at
+// condition 1e8 in FP64 (768 x 768 x 1024, tanh 3.0).
+//
+// The recurrence is a chain over the rows, but each of its three parts composes:
+//   pivots: q_k = g_k / d_k = (s + a q) / (s + a q + c), s = -sigma, a Moebius map
+//     of q_{k-1} with the matrix [[a, s], [a, s + c]], whose entries and
+//     products are all positive: products lose no accuracy (n, d kept in range by
+//     powers of two).  With q = n / d, -d_k = d'/d for the mapped denominator d'.
+//   forward y_k = (a_k / -d_k) y_{k-1} - f_k / -d_k and
+//   backward x_k = y_k + (c_k / -d_k) x_{k+1}: affine maps with factors in [0, 1].
+// So a line is cut into PS chunks of L rows, one per lane: compose the chunk,
+// Kogge-Stone scan over the chunks (in LDS), then the chunk's rows from the
+// value that enters it.  One lane per line walking all rows took 0.26 us per
+// row (the latency of one chain): at 256 x 256 x 384 in FP32 100 us beside 50 us
+// for all other lines, 57 us for both now; at 64^3 the z solve with the zero mode in a
+// launch of its own on a second stream took about 40 us between its
+// neighbours, 7 us now.
+//
+// LDS: 2 PS L + 4 NTS doubles.  Threads beyond NTS repeat the work of the
+// first NTS (same values to the same slots) and do not store.
+// ---------------------------------------------------------------------------
+// n and d (or two columns of them) scaled by a common power of two, d near 1
+__device__ __forceinline__ void renorm(double& n, double& d) {
+    const int e = -__builtin_amdgcn_frexp_exp(d);
+    n = __builtin_ldexp(n, e);
+    d = __builtin_ldexp(d, e);
+}
+__device__ __forceinline__ void renorm2(double& n0, double& d0, double& n1, double& d1) {
+    const int e = -__builtin_amdgcn_frexp_exp(d0 + d1);
+    n0 = __builtin_ldexp(n0, e);
+    d0 = __builtin_ldexp(d0, e);
+    n1 = __builtin_ldexp(n1, e);
+    d1 = __builtin_ldexp(d1, e);
+}
+
+template <int NT>
+constexpr int zspec_threads() { return NT < 512 ? NT : 512; }
+// chunks and rows per chunk of the special lines beside tiles of pmax chunks of
+// l rows: twice as many half as long for 16 rows and more (a lane holds two
+// FP64 values per row; with 24 rows the tiles' kernels spilled)
+constexpr int zspec_chunks(int pmax, int l) { return l <= 12 ? pmax : 2 * pmax; }
+constexpr int zspec_rows(int l) { return l <= 12 ? l : l / 2; }
+template <int PMAX, int L, int NT>
+constexpr int zspec_lds() { return (2 * PMAX * L + 4 * zspec_threads<NT>()) * (int)sizeof(double); }
+
+template <typename TS, typename TC, int PS, int L, int NT>
+__device__ __forceinline__ void z_lines(const ZArgs<TS, TC>& a, int grp, double* lds) {
+    constexpr int NTS = zspec_threads<NT>(), LN = NTS / PS;
+    static_assert(LN >= 1 && NTS % PS == 0 && NT % NTS == 0, "whole lines per group");
+    double* ca = lds;
+    double* cc = lds + PS * L;
+    double* ex = lds + 2 * PS * L;   // [4][NTS]
+    const int nz = a.nz;
+    for (int k = threadIdx.x; k < PS * L; k += NT) {
+        ca[k] = (k > 0 && k < nz) ? a.za64[k] : 0.0;
+        cc[k] = (k + 1 < nz) ? a.zc64[k] : 0.0;
+    }
+    const int me = threadIdx.x % NTS;
+    const int ln = me % LN, p = me / LN;
+    const int li = grp * LN + ln;
+    const bool own = li < a.nlist;
+    const int line = a.list[own ? li : a.nlist - 1];
+    const int qy = line / a.nx, qx = line - qy * a.nx;
+    const double s = -(a.lamx64[qx] + a.lamy64[qy]);
+    const size_t st = (size_t)a.nx * a.ny;
+    TS* col = a.data + line;
+    const int s0 = p * L;
+    double f[L], r[L];
+#pragma unroll
+    for (int t = 0; t < L; ++t) {
+        const int k = s0 + t < nz ? s0 + t : nz - 1;
+        const double v = (double)col[(size_t)k * st];
+        f[t] = s0 + t < nz ? v * (a.transposed ? a.scale64 * a.inv_dz64[k] : a.scale64) : 0.0;
+    }
+    __syncthreads();
+    // the chunk's Moebius matrix, as the images of (n, d) = (1, 0) and (0, 1)
+    double n0 = 1.0, d0 = 0.0, n1 = 0.0, d1 = 1.0;
+#pragma unroll
+    for (int t = 0; t < L; ++t) {
+        const double A = ca[s0 + t], C = cc[s0 + t];
+        n0 = A * n0 + s * d0;
+        d0 = C * d0 + n0;
+        n1 = A * n1 + s * d1;
+        d1 = C * d1 + n1;
+        if (t % 4 == 3) renorm2(n0, d0, n1, d1);
+    }
+    for (int o = 1; o < PS; o <<= 1) {
+        __syncthreads();
+        ex[me] = n0;
+        ex[NTS + me] = d0;
+        ex[2 * NTS + me] = n1;
+        ex[3 * NTS + me] = d1;
+        __syncthreads();
+        if (p >= o) {
+            const int w = me - o * LN;
+            const double sn0 = ex[w], sd0 = ex[NTS + w], sn1 = ex[2 * NTS + w], sd1 = ex[3 * NTS + w];
+            const double a0 = n0 * sn0 + n1 * sd0, b0 = d0 * sn0 + d1 * sd0;
+            const double a1 = n0 * sn1 + n1 * sd1, b1 = d0 * sn1 + d1 * sd1;
+            n0 = a0;
+            d0 = b0;
+            n1 = a1;
+            d1 = b1;
+            renorm2(n0, d0, n1, d1);
+        }
+    }
+    __syncthreads();
+    ex[me] = n0 + n1;          // the line starts from q = 1 (a_0 = 0: it has no effect)
+    ex[NTS + me] = d0 + d1;
+    __syncthreads();
+    double n = 1.0, d = 1.0;
+    if (p > 0) {
+        n = ex[me - LN];
+        d = ex[NTS + me - LN];
+    }
+    double Y = 0.0, Q = 1.0;   // the chunk's forward map: y_out = Q y_in + Y
+#pragma unroll
+    for (int t = 0; t < L; ++t) {
+        const double A = ca[s0 + t], C = cc[s0 + t];
+        const double t0 = A * n + s * d;
+        const double dn = C * d + t0;
+        r[t] = d * zrcp(dn);   // 1 / -d_k
+        n = t0;
+        d = dn;
+        if (t % 4 == 3) renorm(n, d);
+        const double al = A * r[t];
+        Y = al * Y - f[t] * r[t];
+        Q *= al;
+    }
+    for (int o = 1; o < PS; o <<= 1) {
+        __syncthreads();
+        ex[me] = Y;
+        ex[NTS + me] = Q;
+        __syncthreads();
+        if (p >= o) {
+            Y = Q * ex[me - o * LN] + Y;
+            Q *= ex[NTS + me - o * LN];
+        }
+    }
+    __syncthreads();
+    ex[me] = Y;
+    __syncthreads();
+    double y = p > 0 ? ex[me - LN] : 0.0;
+#pragma unroll
+    for (int t = 0; t < L; ++t) {
+        y = ca[s0 + t] * r[t] * y - f[t] * r[t];
+        f[t] = y;
+    }
+    double X = 0.0;
+    Q = 1.0;
+#pragma unroll
+    for (int t = L - 1; t >= 0; --t) {
+        r[t] *= cc[s0 + t];    // c_k / -d_k from here on
+        X = r[t] * X + f[t];
+        Q *= r[t];
+    }
+    for (int o = 1; o < PS; o <<= 1) {
+        __syncthreads();
+        ex[me] = X;
+        ex[NTS + me] = Q;
+        __syncthreads();
+        if (p + o < PS) {
+            X = Q * ex[me + o * LN] + X;
+            Q *= ex[NTS + me + o * LN];
+        }
+    }
+    __syncthreads();
+    ex[me] = X;
+    __syncthreads();
+    double x = p + 1 < PS ? ex[me + LN] : 0.0;
+#pragma unroll
+    for (int t = L - 1; t >= 0; --t) {
+        x = r[t] * x + f[t];
+        f[t] = x;
+    }
+    if (own && threadIdx.x < NTS) {
+#pragma unroll
+        for (int t = 0; t < L; ++t)
+            if (s0 + t < nz) col[(size_t)(s0 + t) * st] = (TS)(a.transposed ? f[t] * a.dz64[s0 + t] : f[t]);
+    }
+    __syncthreads();           // the caller reuses the LDS
+}
+
+// ---------------------------------------------------------------------------
+// (0,0) mode: singular z line (zero-flux walls).  Removes the dz-weighted
+// mean of the scaled right-hand side (compatibility), integrates the flux
+// F_k = sum_{k'<k} dz_k' f_k', sums p_k = sum_{k'<=k} h_k' F_k', and pins
+// sum dz_k p_k = 0.  One workgroup, FP64, prefix sums by wave shuffles.
+// ---------------------------------------------------------------------------
+// sum of the values of all lower threads; total: of all threads
+template <int NT>
+__device__ __forceinline__ double block_exscan(double v, double* sh, double& total) {
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    double inc = v;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const double w = __shfl_up(inc, o, 64);
+        if (lane >= o) inc += w;
+    }
+    double exc = __shfl_up(inc, 1, 64);
+    if (lane == 0) exc = 0.0;
+    __syncthreads();
+    if (lane == 63) sh[wid] = inc;
+    __syncthreads();
+    double pre = 0.0;
+    total = 0.0;
+#pragma unroll
+    for (int w = 0; w < NT / 64; ++w) {
+        if (w == wid) pre = total;
+        total += sh[w];
+    }
+    return pre + exc;
+}
+
+template <typename TS, typename TC, int NT>
+__device__ __forceinline__ void z_zero_mode(const ZArgs<TS, TC>& a, double* sh) {
+    constexpr int CMAX = (kMaxNz + NT - 1) / NT;
+    const int nz = a.nz;
+    const int c = (nz + NT - 1) / NT;
+    const int k0 = threadIdx.x * c;
+    const size_t st = (size_t)a.nx * a.ny;
+    double f[CMAX], w[CMAX], h[CMAX];
+    double loc = 0.0, total, total2;
+#pragma unroll
+    for (int r = 0; r < CMAX; ++r) {
+        const int k = k0 + r;
+        const bool in = r < c && k < nz;
+        f[r] = in ? (double)a.data[(size_t)k * st] * (a.transposed ? a.scale64 * a.inv_dz64[k] : a.scale64) : 0.0;
+        w[r] = in ? a.dz64[k] : 0.0;
+        h[r] = in ? a.h64[k] : 0.0;   // h_0 = 0
+        loc += w[r] * f[r];
+    }
+    block_exscan<NT>(loc, sh, total);
+    const double mean = total / a.lz;
+    loc = 0.0;
+#pragma unroll
+    for (int r = 0; r < CMAX; ++r) {
+        f[r] -= mean;
+        loc += w[r] * f[r];
+    }
+    double run = block_exscan<NT>(loc, sh, total2);   // flux entering this thread's first row
+    loc = 0.0;
+#pragma unroll
+    for (int r = 0; r < CMAX; ++r) {
+        h[r] *= run;
+        run += w[r] * f[r];
+        loc += h[r];
+    }
+    run = block_exscan<NT>(loc, sh, total2);
+    loc = 0.0;
+#pragma unroll
+    for (int r = 0; r < CMAX; ++r) {
+        run += h[r];
+        f[r] = run;
+        loc += w[r] * f[r];
+    }
+    block_exscan<NT>(loc, sh, total);
+    const double pm = total / a.lz;
+#pragma unroll
+    for (int r = 0; r < CMAX; ++r) {
+        const int k = k0 + r;
+        if (r < c && k < nz) {
+            double v = f[r] - pm;
+            if (a.transposed) v *= w[r];
+            a.data[(size_t)k * st] = (TS)v;
+        }
+    }
+    if (threadIdx.x == 0 && a.scal) a.scal[0] = mean;
+    __syncthreads();           // the caller reuses the LDS
+}
+
+// group g of the special lines, by a whole workgroup of a kernel whose tiles
+// have PMAX chunks of L rows
+template <typename TS, typename TC, int PMAX, int L, int NT>
+__device__ __forceinline__ void z_special(const ZArgs<TS, TC>& a, int g, void* lds) {
+    if (g == 0) z_zero_mode<TS, TC, NT>(a, static_cast<double*>(lds));
+    else z_lines<TS, TC, zspec_chunks(PMAX, L), zspec_rows(L), NT>(a, g - 1, static_cast<double*>(lds));
+}
+
+// The special lines by themselves, where they are more than one group per CU:
+// here two workgroups fit a CU, beside the tiles of long lines one (the solve
+// of 768 x 768 x 1024, 14.5 thousand lines: 10.95 ms with them in the tiles'
+// launch, 10.73 ms so)
+template <typename TS, typename TC, int PS, int L>
+__global__ __launch_bounds__(512, 4) void k_zspecial(ZArgs<TS, TC> a) {
+    __shared__ double lds[zspec_lds<PS, L, 512>() / sizeof(double)];
+    if (blockIdx.x == 0) z_zero_mode<TS, TC, 512>(a, lds);
+    else z_lines<TS, TC, PS, L, 512>(a, blockIdx.x - 1, lds);
+}
 
 template <typename TS, typename TC, int TXL, int L, int NT>
 __global__ __launch_bounds__(NT) void k_zsolve(ZArgs<TS, TC> a) {
     constexpr int PMAX = NT / TXL;
-    __shared__ TC sh[4][NT];
-    __shared__ TC ta[PMAX * L], tc[PMAX * L], tb[PMAX * L], tm[PMAX * L], tsi[PMAX * L], tso[PMAX * L];
+    struct Lds {
+        TC sh[4][NT];
+        TC ta[PMAX * L], tc[PMAX * L], tb[PMAX * L], tm[PMAX * L], tsi[PMAX * L], tso[PMAX * L];
+    };
+    static_assert(sizeof(Lds) >= zspec_lds<PMAX, L, NT>(), "the special lines fit the tile's LDS");
+    __shared__ __align__(16) unsigned char lds[sizeof(Lds)];
+    if ((int)blockIdx.x < a.nspec) {
+        z_special<TS, TC, PMAX, L, NT>(a, blockIdx.x, lds);
+        return;
+    }
+    Lds& sm = *reinterpret_cast<Lds*>(lds);
+    auto& sh = sm.sh;
+    TC *ta = sm.ta, *tc = sm.tc, *tb = sm.tb, *tm = sm.tm, *tsi = sm.tsi, *tso = sm.tso;
     const int nx = a.nx, nz = a.nz, P = a.P;
     const int npad = P * L;
     // per-k coefficients staged in LDS, padded to P*L rows with decoupled
@@ -98,8 +418,9 @@ __global__ __launch_bounds__(NT) void k_zsolve(ZArgs<TS, TC> a) {
     const int ln = threadIdx.x % TXL;
     const int p = threadIdx.x / TXL;
     const size_t stride = (size_t)nx * a.ny;
-    const int qx = blockIdx.x * TXL + ln;
-    const int qy = blockIdx.y;
+    const int tile = (int)blockIdx.x - a.nspec;
+    const int qy = tile / a.gx;
+    const int qx = (tile - qy * a.gx) * TXL + ln;
     bool active = qx < nx;
     TC sigma = (TC)-1;
     if (active) {
@@ -249,8 +570,19 @@ template <typename TS, typename TC, int M, int TXLM, int L, int NT>
 __global__ __launch_bounds__(NT) void k_zsolvev(ZArgs<TS, TC> a) {
     using V = typename VecM<TS, M>::type;
     constexpr int PMAX = NT / TXLM;
-    __shared__ TC sh[4][M * NT];
-    __shared__ TC ta[PMAX * L], tc[PMAX * L], tb[PMAX * L], tm[PMAX * L], tsi[PMAX * L], tso[PMAX * L];
+    struct Lds {
+        TC sh[4][M * NT];
+        TC ta[PMAX * L], tc[PMAX * L], tb[PMAX * L], tm[PMAX * L], tsi[PMAX * L], tso[PMAX * L];
+    };
+    static_assert(sizeof(Lds) >= zspec_lds<PMAX, L, NT>(), "the special lines fit the tile's LDS");
+    __shared__ __align__(16) unsigned char lds[sizeof(Lds)];
+    if ((int)blockIdx.x < a.nspec) {
+        z_special<TS, TC, PMAX, L, NT>(a, blockIdx.x, lds);
+        return;
+    }
+    Lds& sm = *reinterpret_cast<Lds*>(lds);
+    auto& sh = sm.sh;
+    TC *ta = sm.ta, *tc = sm.tc, *tb = sm.tb, *tm = sm.tm, *tsi = sm.tsi, *tso = sm.tso;
     const int nx = a.nx, nz = a.nz, P = a.P;
     const int npad = P * L;
     for (int k = threadIdx.x; k < npad; k += NT) {
@@ -264,8 +596,9 @@ __global__ __launch_bounds__(NT) void k_zsolvev(ZArgs<TS, TC> a) {
     }
     const int ln = threadIdx.x % TXLM;
     const int p = threadIdx.x / TXLM;
-    const int qx0 = (blockIdx.x * TXLM + ln) * M;
-    const int qy = blockIdx.y;
+    const int tile = (int)blockIdx.x - a.nspec;
+    const int qy = tile / a.gx;
+    const int qx0 = ((tile - qy * a.gx) * TXLM + ln) * M;
     const size_t strideV = (size_t)nx * a.ny / M;   // in vectors
     bool act[M];
     TC sigma[M];
@@ -477,9 +810,18 @@ __global__ __launch_bounds__(NT) void k_zsolvev_pf(ZArgs<TS, TC> a) {
     constexpr int NZ = P * L;
     typedef __attribute__((address_space(3))) void* lds_void;
     typedef const __attribute__((address_space(1))) void* glb_void;
-    __shared__ TC sh[4][M * NT];
-    __shared__ TC ta[NZ], tc[NZ], tb[NZ], tso[NZ];
-    __shared__ V pf[S][NT];
+    struct Lds {
+        TC sh[4][M * NT];
+        TC ta[NZ], tc[NZ], tb[NZ], tso[NZ];
+        V pf[S][NT];
+    };
+    static_assert(sizeof(Lds) >= zspec_lds<P, L, NT>(), "the special lines fit the tile's LDS");
+    __shared__ __align__(16) unsigned char lds[sizeof(Lds)];
+    for (int g = blockIdx.x; g < a.nspec; g += gridDim.x) z_special<TS, TC, P, L, NT>(a, g, lds);
+    Lds& sm = *reinterpret_cast<Lds*>(lds);
+    auto& sh = sm.sh;
+    auto& pf = sm.pf;
+    TC *ta = sm.ta, *tc = sm.tc, *tb = sm.tb, *tso = sm.tso;
     const int nx = a.nx;
     for (int k = threadIdx.x; k < NZ; k += NT) {
         ta[k] = a.za[k];
@@ -691,242 +1033,6 @@ __global__ __launch_bounds__(NT) void k_zsolvev_pf(ZArgs<TS, TC> a) {
         sync_lds_nofence();   // sh is rewritten by the next tile
     }
     __builtin_amdgcn_s_waitcnt(0);   // the last direct loads land before the workgroup's LDS is released
-}
-
-// ---------------------------------------------------------------------------
-// Near-singular mode lines: |lambda_x + lambda_y| below the plan's threshold
-// (condition 1 + 4 / (dz_min^2 |sigma|) above 1e4).  One lane per line,
-// sequential Thomas in FP64 with the pivots in row-sum form.  With zero-flux
-// walls every row of L_z + sigma sums to sigma, so the pivot
-//     d_k = b_k - a_k c_{k-1} / d_{k-1},   b_k = -(a_k + c_k) + sigma,
-// equals g_k - c_k with g_k = sigma - a_k g_{k-1} / d_{k-1}, g_0 = sigma: every
-// term has the sign of sigma, nothing cancels.  Forming b_k first rounds the
-// small sigma against a_k + c_k, which costs up to ~1e-11 relative error at
-// condition 1e8 in FP64 (768 x 768 x 1024, tanh 3.0); this form stays at
-// ~1e-15.  The eliminated right-hand side and the ratios c_k / d_k go to an
-// FP64 scratch (line-contiguous across lanes: coalesced), the back
-// substitution writes the field.
-// ---------------------------------------------------------------------------
-template <typename TS>
-struct ZSeqArgs {
-    int nx, nz, nlist, transposed;
-    size_t stride;          // nx * ny
-    TS* data;
-    const int* list;        // line indices qy * nx + qx, ascending
-    double* ys;             // scratch, nlist * nz: eliminated right-hand side
-    double* cps;            // scratch, nlist * nz: c_k / d_k
-    const double* za;
-    const double* zc;
-    const double* lamx;
-    const double* lamy;
-    const double* dz;       // transposed solve: input scaled by 1/dz_k, output by dz_k
-    double scale;           // 1 / (nx ny)
-};
-
-template <typename TS>
-__global__ __launch_bounds__(64) void k_zline_seq(ZSeqArgs<TS> a) {
-    // The per-row coefficients go to LDS first (uniform reads there, off the
-    // critical path of the recurrences).  Rows go in batches of B with the
-    // next batch's loads issued before the current batch is eliminated; the
-    // batch bodies have no branches (row indices of loads are clamped into
-    // the line, and the last nz % B rows are a separate tail), so the
-    // compiler waits only for the batch it uses.
-    constexpr int B = 16;
-    __shared__ double sa[kMaxNz], sc[kMaxNz], si[kMaxNz], so[kMaxNz];
-    const int nz = a.nz, nl = a.nlist;
-    for (int k = threadIdx.x; k < nz; k += 64) {
-        sa[k] = (k > 0) ? a.za[k] : 0.0;
-        sc[k] = (k + 1 < nz) ? a.zc[k] : 0.0;
-        si[k] = a.transposed ? a.scale / a.dz[k] : a.scale;
-        so[k] = a.transposed ? a.dz[k] : 1.0;
-    }
-    __syncthreads();
-    const int li = blockIdx.x * 64 + threadIdx.x;
-    if (li >= nl) return;
-    const int line = a.list[li];
-    const int qy = line / a.nx, qx = line - qy * a.nx;
-    const double sigma = a.lamx[qx] + a.lamy[qy];
-    const TS* __restrict__ colr = a.data + line;
-    TS* __restrict__ colw = a.data + line;
-    const size_t st = a.stride;
-    double* __restrict__ ys = a.ys + li;
-    double* __restrict__ cps = a.cps + li;
-    const int nfull = nz - nz % B;
-    auto load_rows = [&](int k0, double* f) {
-#pragma unroll
-        for (int t = 0; t < B; ++t) {
-            const int k = (k0 + t < nz) ? k0 + t : nz - 1;   // clamped (the value is then unused)
-            f[t] = (double)colr[(size_t)k * st];
-        }
-    };
-    double q = 1.0, y = 0.0;   // q = g_{k-1} / d_{k-1} (1 before the first row)
-    auto fwd_row = [&](int k, double f) {
-        const double A = sa[k], C = sc[k];
-        const double g = sigma - A * q;
-        const double r = zrcp(g - C);
-        q = g * r;
-        y = (f * si[k] - A * y) * r;
-        ys[(size_t)k * nl] = y;
-        cps[(size_t)k * nl] = C * r;
-    };
-    double fa[B], fb[B];
-    load_rows(0, fa);
-    for (int k0 = 0; k0 < nfull; k0 += B) {
-        load_rows(k0 + B, fb);
-#pragma unroll
-        for (int t = 0; t < B; ++t) fwd_row(k0 + t, fa[t]);
-#pragma unroll
-        for (int t = 0; t < B; ++t) fa[t] = fb[t];
-    }
-#pragma unroll
-    for (int t = 0; t < B; ++t)
-        if (nfull + t < nz) fwd_row(nfull + t, fa[t]);
-    // back substitution, top row first: the tail, then the full batches
-    auto load_back = [&](int k1, double* yv, double* cv) {   // rows k1, k1 - 1, ..., k1 - B + 1
-#pragma unroll
-        for (int t = 0; t < B; ++t) {
-            const int k = (k1 - t >= 0) ? k1 - t : 0;
-            yv[t] = ys[(size_t)k * nl];
-            cv[t] = cps[(size_t)k * nl];
-        }
-    };
-    double x = 0.0;
-    auto back_row = [&](int k, double yk, double ck) {
-        x = yk - ck * x;
-        colw[(size_t)k * st] = (TS)(x * so[k]);
-    };
-    double ya[B], ca[B], yb[B], cb[B];
-    load_back(nz - 1, ya, ca);
-    if (nfull > 0) load_back(nfull - 1, yb, cb);
-    const int rem = nz - nfull;
-#pragma unroll
-    for (int t = 0; t < B; ++t)
-        if (t < rem) back_row(nz - 1 - t, ya[t], ca[t]);
-    for (int k1 = nfull - 1; k1 >= 0; k1 -= B) {
-#pragma unroll
-        for (int t = 0; t < B; ++t) {
-            ya[t] = yb[t];
-            ca[t] = cb[t];
-        }
-        load_back(k1 - B, yb, cb);
-#pragma unroll
-        for (int t = 0; t < B; ++t) back_row(k1 - t, ya[t], ca[t]);
-    }
-}
-
-// ---------------------------------------------------------------------------
-// (0,0) mode: singular z line (zero-flux walls).  Removes the dz-weighted
-// mean of the scaled right-hand side (compatibility), integrates the flux
-// F_k = sum_{k'<k} dz_k' f_k', sums p_k = sum_{k'<=k} h_k' F_k', and pins
-// sum dz_k p_k = 0.  One workgroup of 256 threads, FP64 arithmetic.
-// ---------------------------------------------------------------------------
-template <typename TS>
-struct ZeroArgs {
-    int nz, transposed;
-    size_t stride;
-    TS* data;
-    double scale, lz;
-    const double* dz;
-    const double* inv_dz;
-    const double* h;
-    double* scal;   // scal[0] <- removed mean (not for the transposed solve)
-};
-
-__device__ __forceinline__ double zm_block_sum(double v, double* sh) {
-    sh[threadIdx.x] = v;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double s = 0.0;
-        for (int t = 0; t < 256; ++t) s += sh[t];
-        sh[256] = s;
-    }
-    __syncthreads();
-    const double r = sh[256];
-    __syncthreads();
-    return r;
-}
-
-__device__ __forceinline__ double zm_block_exscan(double v, double* sh) {
-    sh[threadIdx.x] = v;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double s = 0.0;
-        for (int t = 0; t < 256; ++t) {
-            const double x = sh[t];
-            sh[t] = s;
-            s += x;
-        }
-    }
-    __syncthreads();
-    const double r = sh[threadIdx.x];
-    __syncthreads();
-    return r;
-}
-
-template <typename TS>
-__global__ __launch_bounds__(256) void k_zero_mode(ZeroArgs<TS> a) {
-    __shared__ double sh[257];
-    constexpr int CMAX = kMaxNz / 256;
-    const int nz = a.nz;
-    const int c = (nz + 255) / 256;
-    const int k0 = threadIdx.x * c;
-    double f[CMAX];
-#pragma unroll
-    for (int r = 0; r < CMAX; ++r) {
-        const int k = k0 + r;
-        f[r] = 0.0;
-        if (r < c && k < nz) {
-            double sc = a.scale;
-            if (a.transposed) sc *= a.inv_dz[k];
-            f[r] = (double)a.data[(size_t)k * a.stride] * sc;
-        }
-    }
-    double loc = 0.0;
-#pragma unroll
-    for (int r = 0; r < CMAX; ++r)
-        if (r < c && k0 + r < nz) loc += a.dz[k0 + r] * f[r];
-    const double mean = zm_block_sum(loc, sh) / a.lz;
-    loc = 0.0;
-#pragma unroll
-    for (int r = 0; r < CMAX; ++r)
-        if (r < c && k0 + r < nz) {
-            f[r] -= mean;
-            loc += a.dz[k0 + r] * f[r];
-        }
-    double run = zm_block_exscan(loc, sh);   // flux entering this thread's first row
-    double hf[CMAX];
-    loc = 0.0;
-#pragma unroll
-    for (int r = 0; r < CMAX; ++r) {
-        hf[r] = 0.0;
-        if (r < c && k0 + r < nz) {
-            const int k = k0 + r;
-            hf[r] = a.h[k] * run;   // h_0 = 0
-            run += a.dz[k] * f[r];
-            loc += hf[r];
-        }
-    }
-    run = zm_block_exscan(loc, sh);
-    loc = 0.0;
-#pragma unroll
-    for (int r = 0; r < CMAX; ++r) {
-        if (r < c && k0 + r < nz) {
-            run += hf[r];
-            f[r] = run;
-            loc += a.dz[k0 + r] * f[r];
-        }
-    }
-    const double pm = zm_block_sum(loc, sh) / a.lz;
-#pragma unroll
-    for (int r = 0; r < CMAX; ++r) {
-        const int k = k0 + r;
-        if (r < c && k < nz) {
-            double v = f[r] - pm;
-            if (a.transposed) v *= a.dz[k];
-            a.data[(size_t)k * a.stride] = (TS)v;
-        }
-    }
-    if (threadIdx.x == 0 && !a.transposed && a.scal) a.scal[0] = mean;
 }
 
 // ---------------------------------------------------------------------------

@@ -172,7 +172,7 @@ struct fsei_plan_impl {
     size_t ws_field2 = 0, ws_field2_bytes = 0;     // second field (refine: FP32 work field)
     size_t ws_field3 = 0, ws_field3_bytes = 0;     // refine: FP64 pressure when the caller passes none
     size_t ws_field4 = 0, ws_field4_bytes = 0;     // refine: FP32 pressure of the first solve
-    size_t ws_list = 0, ws_list_bytes = 0;         // near-singular mode lines (sequential FP64 solver)
+    size_t ws_list = 0, ws_list_bytes = 0;         // near-singular mode lines
     // implicit viscous step: chunk length per direction (x, y, z; 0 when a
     // line is longer than kViscMaxN), the table blocks of the three
     // components (x, y, z blocks each), and the beta each component's
@@ -186,22 +186,14 @@ struct fsei_plan_impl {
     static constexpr int kScalars = 64;
 
     // lines with |lambda_x + lambda_y| < sigma_thr (condition number above
-    // kappa_star) are solved one per lane in FP64 with row-sum pivots
+    // kappa_star) are solved in FP64 with row-sum pivots
     double sigma_thr = 0.0;
-    size_t ws_seq = 0;   // FP64 scratch of the near-singular line solver
     std::vector<int> list_host;
     int nlist = 0;
 
     void* ws = nullptr;
     size_t ws_bytes = 0;
     void* stream = nullptr;
-    // side stream of the z solve (near-singular and (0,0) lines run there,
-    // concurrently with the tiled lines) and its fork / join events; created
-    // with the first workspace, destroyed with the plan
-    void* side_stream = nullptr;
-    void* ev_fork = nullptr;
-    void* ev_join = nullptr;
-
     // timing
     bool timing = false;
     double t_ms[FSEI_NUM_KERNEL_SLOTS] = {0};

@@ -147,7 +147,7 @@ class Plan:
         if workspace:
             # workspace=False: a plan for project_noalloc only (no device memory)
             self._ws = torch.empty(max(self.workspace_bytes, 256), dtype=torch.uint8, device=self.device)
-            with torch.cuda.device(self.device):   # the plan's side stream is made on its device
+            with torch.cuda.device(self.device):
                 _check(L.fsei_plan_set_workspace(h, _ptr(self._ws), self.workspace_bytes), "fsei_plan_set_workspace")
 
     @classmethod
