@@ -13,11 +13,13 @@ LIB = os.path.join(PKG, "libfsei.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 SOURCES = ["fsei_api.hip", "fsei_plan.cpp"]
-HEADERS = ["fsei_plan.h", "fsei_fft.h", "fsei_transforms.h", "fsei_lengths.h", "fsei_kernels.h", "fsei_viscous.h",
+HEADERS = ["fsei_plan.h", "fsei_fft.h", "fsei_transforms.h", "fsei_lengths.h", "fsei_z.h", "fsei_kernels.h", "fsei_viscous.h",
            "fsei_momentum.h", "fsei_ibm.h"]
 # fsei_len.hip holds the transform kernels of one length and is compiled once
 # per length with kernels of its own: every 2^a 3^b from 16 to 1024
 LENGTH_SOURCE = "fsei_len.hip"
+# fsei_z.hip holds the z solves of one type
+Z_SOURCE = "fsei_z.hip"
 LENGTHS = sorted(2 ** a * 3 ** b for a in range(11) for b in range(7) if 16 <= 2 ** a * 3 ** b <= 1024)
 
 # -packed-fp32-ops: hipcc -O3 may otherwise emit packed FP32 instructions
@@ -33,11 +35,12 @@ def build(verbose: bool = True) -> str:
     include = ["-I", os.path.join(PKG, "..", "include")]
     objdir = tempfile.mkdtemp(prefix="fsei_build_")
     try:
-        jobs = [(s, []) for s in SOURCES] + [(LENGTH_SOURCE, [f"-DFSEI_LEN={n}"]) for n in reversed(LENGTHS)]
+        jobs = [(s, []) for s in SOURCES] + [(Z_SOURCE, [f"-DFSEI_REAL={t}"]) for t in ("double", "float")]
+        jobs += [(LENGTH_SOURCE, [f"-DFSEI_LEN={n}"]) for n in reversed(LENGTHS)]
 
         def compile_one(job):
             src, defs = job
-            obj = os.path.join(objdir, src.split(".")[0] + "".join(defs).replace("-DFSEI_LEN=", "_") + ".o")
+            obj = os.path.join(objdir, src.split(".")[0] + "".join(d.split("=")[1] for d in defs) + ".o")
             cmd = [HIPCC, *FLAGS, *defs, *include, "-c", os.path.join(CSRC, src), "-o", obj]
             if verbose:
                 print(" ".join(cmd), flush=True)

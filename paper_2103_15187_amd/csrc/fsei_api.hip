@@ -13,6 +13,7 @@
 
 #include "fsei_kernels.h"
 #include "fsei_lengths.h"
+#include "fsei_z.h"
 #include "fsei_plan.h"
 #include "fsei_viscous.h"
 #include "fsei_momentum.h"
@@ -405,8 +406,6 @@ void launch_y(fsei_plan* p, T* data, bool inverse) {
     else if constexpr (sizeof(T) == 8) launch_y_cfg<T, 4096, 512>(p, a, inverse);
 }
 
-// chunking of the z lines: P chunks of exactly L rows (L one of the compiled
-// sizes), the last chunk padded with decoupled rows; P <= pmax
 // compute units of the current device (cached per device; 256 if the query fails)
 int cus_of_current_device() {
     constexpr int kDevs = 64;
@@ -419,74 +418,6 @@ int cus_of_current_device() {
         cus[dev].store(n, std::memory_order_relaxed);
     }
     return n;
-}
-
-bool choose_chunks(int nz, int pmax, int* L, int* P) {
-    static const int sizes[] = {4, 8, 12, 16, 24, 32};
-    for (int l : sizes) {
-        const int pc = (nz + l - 1) / l;
-        if (pc <= pmax) {
-            *L = l;
-            *P = pc;
-            return true;
-        }
-    }
-    return false;
-}
-
-template <typename TS, typename TC, int PS, int L>
-void launch_zspecial(fsei_plan* p, const ZArgs<TS, TC>& a) {
-    constexpr int LN = 512 / PS;
-    Timed t(p, K_ZLIST);
-    hipLaunchKernelGGL((k_zspecial<TS, TC, PS, L>), dim3(1u + (unsigned)((a.nlist + LN - 1) / LN)), dim3(512), 0, S(p),
-                       a);
-}
-
-// grid of a z solve: the groups of special lines, then gx tiles per row of
-// modes.  Groups that would take the tiles' launch more than one round of the
-// CUs go ahead in a launch of their own.
-template <int PMAX, int NT, typename TS, typename TC>
-dim3 z_grid(fsei_plan* p, ZArgs<TS, TC>* a, int gx) {
-    const int ln = zspec_threads<NT>() / zspec_chunks(PMAX, a->L);
-    a->gx = gx;
-    a->nspec = 1 + (a->nlist + ln - 1) / ln;
-    if (a->nspec > cus_of_current_device()) {
-        if (a->nz <= 256) launch_zspecial<TS, TC, 64, 4>(p, *a);
-        else if (a->nz <= 512) launch_zspecial<TS, TC, 64, 8>(p, *a);
-        else if (a->nz <= 1024) launch_zspecial<TS, TC, 64, 16>(p, *a);
-        else launch_zspecial<TS, TC, 128, 16>(p, *a);
-        a->nspec = 0;
-    }
-    return dim3((unsigned)a->nspec + (unsigned)gx * (unsigned)a->ny);
-}
-
-template <typename TS, typename TC, int TXL, int NT>
-void z_dispatch(fsei_plan* p, ZArgs<TS, TC> a) {
-    const size_t dyn = 0;
-    const dim3 grid = z_grid<NT / TXL, NT>(p, &a, (p->nx + TXL - 1) / TXL);
-    Timed t(p, K_ZSOLVE);
-    switch (a.L) {
-        case 4: hipLaunchKernelGGL((k_zsolve<TS, TC, TXL, 4, NT>), grid, dim3(NT), dyn, S(p), a); break;
-        case 8: hipLaunchKernelGGL((k_zsolve<TS, TC, TXL, 8, NT>), grid, dim3(NT), dyn, S(p), a); break;
-        case 12: hipLaunchKernelGGL((k_zsolve<TS, TC, TXL, 12, NT>), grid, dim3(NT), dyn, S(p), a); break;
-        case 16: hipLaunchKernelGGL((k_zsolve<TS, TC, TXL, 16, NT>), grid, dim3(NT), dyn, S(p), a); break;
-        case 24: hipLaunchKernelGGL((k_zsolve<TS, TC, TXL, 24, NT>), grid, dim3(NT), dyn, S(p), a); break;
-        default: hipLaunchKernelGGL((k_zsolve<TS, TC, TXL, 32, NT>), grid, dim3(NT), dyn, S(p), a); break;
-    }
-}
-
-template <typename TS, typename TC, int M, int TXLM, int NT>
-void zv_dispatch(fsei_plan* p, ZArgs<TS, TC> a) {
-    const dim3 grid = z_grid<NT / TXLM, NT>(p, &a, (p->nx / M + TXLM - 1) / TXLM);
-    Timed t(p, K_ZSOLVE);
-    switch (a.L) {
-        case 4: hipLaunchKernelGGL((k_zsolvev<TS, TC, M, TXLM, 4, NT>), grid, dim3(NT), 0, S(p), a); break;
-        case 8: hipLaunchKernelGGL((k_zsolvev<TS, TC, M, TXLM, 8, NT>), grid, dim3(NT), 0, S(p), a); break;
-        case 12: hipLaunchKernelGGL((k_zsolvev<TS, TC, M, TXLM, 12, NT>), grid, dim3(NT), 0, S(p), a); break;
-        case 16: hipLaunchKernelGGL((k_zsolvev<TS, TC, M, TXLM, 16, NT>), grid, dim3(NT), 0, S(p), a); break;
-        case 24: hipLaunchKernelGGL((k_zsolvev<TS, TC, M, TXLM, 24, NT>), grid, dim3(NT), 0, S(p), a); break;
-        default: hipLaunchKernelGGL((k_zsolvev<TS, TC, M, TXLM, 32, NT>), grid, dim3(NT), 0, S(p), a); break;
-    }
 }
 
 template <typename TS, typename TC>
@@ -522,89 +453,16 @@ ZArgs<TS, TC> zargs(const fsei_plan* p, TS* data, int transposed, bool record_me
 }
 
 // z solve of every mode line of `data` (in place), zero mode included
-template <typename TS>
-void launch_z(fsei_plan* p, TS* data, int transposed, bool record_mean) {
-    constexpr bool F32 = std::is_same<TS, float>::value;
-    const int nz = p->nz;
-    // Tilings (all do the same arithmetic; chosen by measurement at
-    // 512 x 512 x 768 and 768 x 768 x 1024): adjacent modes per lane as one
-    // vector where nx allows, at most 32 chunks per line; lines longer than
-    // 768 rows (chunks of 32 rows) keep one FP64 mode per lane or take 64
-    // FP32 chunks of at most 16 rows, which avoids register spills.
-    int L = 0, P = 0;
-    const bool c32 = choose_chunks(nz, 32, &L, &P);
-    // The near-singular lines and the (0,0) line are disjoint from the lines
-    // of the tiles; the first workgroups of the same launch take them.
-    if constexpr (!F32) {
-        ZArgs<double, double> a = zargs<double, double>(p, data, transposed, record_mean);
-        if (!transposed && c32 && L == 24 && P == 32 && nz == L * P && p->nx % 32 == 0 && aligned16(data)) {
-            // whole 32-mode tiles of 768 rows: the persistent kernel with the
-            // next tile's first 12 rows of each chunk staged in LDS (0.84 -> 0.66
-            // ms at 512x512x768), one workgroup per CU
-            a.L = L;
-            a.P = P;
-            z_grid<32, 512>(p, &a, p->nx / 32);
-            Timed t(p, K_ZSOLVE);
-            const long ntiles = (long)(p->nx / 32) * p->ny;
-            const int cus = cus_of_current_device();
-            const unsigned g = (unsigned)(ntiles < cus ? ntiles : cus);
-            hipLaunchKernelGGL((k_zsolvev_pf<double, double, 2, 16, 24, 512, 12>), dim3(g), dim3(512), 0, S(p), a);
-        } else if (c32 && L <= 24 && p->nx % 2 == 0) {
-            a.L = L;
-            a.P = P;
-            zv_dispatch<double, double, 2, 16, 512>(p, a);
-        } else if (c32) {
-            a.L = L;
-            a.P = P;
-            z_dispatch<double, double, 16, 512>(p, a);
-        } else {
-            choose_chunks(nz, 64, &L, &P);
-            a.L = L;
-            a.P = P;
-            z_dispatch<double, double, 8, 512>(p, a);
-        }
-    } else {
-        ZArgs<float, float> a = zargs<float, float>(p, data, transposed, record_mean);
-        if (!transposed && c32 && L == 24 && P == 32 && nz == L * P && p->nx % 64 == 0 && aligned16(data)) {
-            // whole 64-mode tiles (256-B rows) of 768 rows: the persistent
-            // kernel, one workgroup per CU, the next tile's first 12 rows of each
-            // chunk staged in LDS (0.39 -> 0.375 ms at 512x512x768 against the
-            // two-workgroup 128-B tiling below)
-            a.L = L;
-            a.P = P;
-            z_grid<32, 512>(p, &a, p->nx / 64);
-            Timed t(p, K_ZSOLVE);
-            const long ntiles = (long)(p->nx / 64) * p->ny;
-            const int cus = cus_of_current_device();
-            const unsigned g = (unsigned)(ntiles < cus ? ntiles : cus);
-            hipLaunchKernelGGL((k_zsolvev_pf<float, float, 4, 16, 24, 512, 12>), dim3(g), dim3(512), 0, S(p), a);
-        } else if (c32 && L <= 24 && p->nx % 4 == 0) {
-            a.L = L;
-            a.P = P;
-            // 8 lanes x 4 modes (128-B rows) in 256-thread workgroups: two
-            // per CU, one solving while the other loads (11 % faster than 16
-            // lanes in 512 threads, one per CU, at 512 x 512 x 768; the FP64
-            // kernel the other way round, 18 % slower)
-            zv_dispatch<float, float, 4, 8, 256>(p, a);
-        } else if (c32 && L <= 24 && p->nx % 2 == 0) {
-            a.L = L;
-            a.P = P;
-            zv_dispatch<float, float, 2, 32, 1024>(p, a);
-        } else if (p->nx % 2 == 0 && choose_chunks(nz, 64, &L, &P)) {
-            a.L = L;
-            a.P = P;
-            zv_dispatch<float, float, 2, 16, 1024>(p, a);
-        } else if (c32) {
-            a.L = L;
-            a.P = P;
-            z_dispatch<float, float, 32, 1024>(p, a);
-        } else {
-            choose_chunks(nz, 64, &L, &P);
-            a.L = L;
-            a.P = P;
-            z_dispatch<float, float, 16, 1024>(p, a);
-        }
+template <typename T>
+void launch_z(fsei_plan* p, T* data, int transposed, bool record_mean) {
+    ZArgs<T, T> a = zargs<T, T>(p, data, transposed, record_mean);
+    const int cus = cus_of_current_device();
+    if (z_tiling<T>(&a, cus)) {
+        Timed t(p, K_ZLIST);
+        z_launch_special<T>(a, S(p));
     }
+    Timed t(p, K_ZSOLVE);
+    z_launch<T>(a, S(p), cus);
 }
 
 // k_grad_row2 with the smallest workgroup that gives every cell pair of a
