@@ -140,6 +140,20 @@ bool pair_tiles(const fsei_plan* p) { return p->nx % 2 == 0 && p->ny % kPairRows
 bool aligned16(const void* q) { return reinterpret_cast<uintptr_t>(q) % 16 == 0; }
 bool al16(const void* q) { return q == nullptr || aligned16(q); }   // optional pointer
 
+// compute units of the current device (cached per device; 256 if the query fails)
+int cus_of_current_device() {
+    constexpr int kDevs = 64;
+    static std::atomic<int> cus[kDevs];
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kDevs) return 256;
+    int n = cus[dev].load(std::memory_order_relaxed);
+    if (n <= 0) {
+        if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) n = 256;
+        cus[dev].store(n, std::memory_order_relaxed);
+    }
+    return n;
+}
+
 // the kernels compiled for length n, or null
 const LenOps* len_ops(int n) {
     switch (n) {
@@ -261,50 +275,80 @@ void set_vel(Args* a, const Vel<T>& q) {
     a->w = q.w;
 }
 
-// fused x inverse + gradient (FP64): nx of a compiled length, whole 8-row
-// tiles, every field 16-byte aligned
-bool xg_ok(const fsei_plan* p, const void* in, const void* pout, const Vel<double>& q) {
-    return (p->nx == 512 || p->nx == 768) && p->ny % kXgRows == 0 && aligned16(in) && al16(pout) && q.aligned();
+// the stencil weights of a gradient correction, or of its adjoint
+template <typename Args>
+void set_grad(const fsei_plan* p, Args* a, bool adjoint, double dt) {
+    using T = decltype(a->cx);
+    if (!adjoint) {
+        a->cx = (T)(-dt / p->dx);
+        a->cy = (T)(-dt / p->dy);
+        a->sw = (T)(-dt);
+        a->bk = tab<T>(p, T_INV_H);
+        a->gk = tab<T>(p, T_INV_H);
+    } else {
+        a->cx = (T)(1.0 / p->dx);
+        a->cy = (T)(1.0 / p->dy);
+        a->sw = (T)1;
+        a->bk = tab<T>(p, T_INV_DZ);
+        a->gk = tab<T>(p, T_GAM_ADJ);
+    }
 }
 
-// planes per workgroup of the fused x inverse + gradient (the chunk's first
-// step re-inverts the plane below it: 1/32 more transform work)
+// most planes per workgroup of the fused x inverses
 constexpr int kXgPlanes = 32;
 
-void launch_xinv_grad(fsei_plan* p, const double* in, double* pout, const Vel<double>& q, bool adjoint, double dt) {
-    XInvGradArgs a{};
+// Fused x inverse + gradient (FP64): a length it is compiled for, whole 8-row
+// tiles, every field aligned to column pairs, and a grid of at least 32 planes
+// of one tile per CU (two passes, us: 256 x 256 x 384 294 -> 274, its adjoint
+// 290 -> 255; 384 x 384 x 500 1002 -> 921, adjoint 1002 -> 834; on small grids
+// the intermediate stays in cache and the two passes are the faster: 128 x 128
+// x 192 42 against 47, 512 x 64 x 64 33 against 231 in 32-plane chunks; in FP32
+// too, 384 x 384 x 500 496 against 590)
+const LenOps* xg_ops(const fsei_plan* p, const void* in, const void* pout, const Vel<double>& q) {
+    const bool ok = xg_len(p->nx) && p->ny % kXgRows == 0 && aligned16(in) && al16(pout) && q.aligned() &&
+                    (long)(p->ny / kXgRows) * p->nz >= 32L * cus_of_current_device();
+    return ok ? len_ops(p->nx) : nullptr;
+}
+
+// Planes per workgroup: the fewest plane steps in all rounds of the CUs, each
+// chunk with `extra` steps more for planes beyond its ends (576 x 384 x 384: 12
+// planes, six whole rounds, 1.10 ms; 18 planes, 4.1 rounds, 1.24 ms)
+int xg_planes(const fsei_plan* p, int per_cu, int extra) {
+    const long slots = (long)per_cu * cus_of_current_device();   // workgroups at a time
+    const long ntj = p->ny / kXgRows;
+    long best = 0;
+    int kc = kXgPlanes;
+    for (int c = kXgPlanes; c >= 6; --c) {
+        const long rounds = (ntj * ((p->nz + c - 1) / c) + slots - 1) / slots;
+        if (best == 0 || rounds * (c + extra) < best) {
+            best = rounds * (c + extra);
+            kc = c;
+        }
+    }
+    return kc;
+}
+
+void launch_xinv_grad(fsei_plan* p, const LenOps* ops, const double* in, double* pout, const Vel<double>& q,
+                      bool adjoint, double dt) {
+    using T = double;
+    XInvGradArgs<T> a{};
     a.ny = p->ny;
     a.nz = p->nz;
     a.bcx = p->bcx;
     a.bcy = p->bcy;
-    a.kc = kXgPlanes;
     a.in = in;
     a.p = pout;
     set_vel(&a, q);
-    if (!adjoint) {
-        a.cx = -dt / p->dx;
-        a.cy = -dt / p->dy;
-        a.sw = -dt;
-        a.bk = tab<double>(p, T_INV_H);
-        a.gk = tab<double>(p, T_INV_H);
-    } else {
-        a.cx = 1.0 / p->dx;
-        a.cy = 1.0 / p->dy;
-        a.sw = 1.0;
-        a.bk = tab<double>(p, T_INV_DZ);
-        a.gk = tab<double>(p, T_GAM_ADJ);
-    }
-    a.twc = tab<double>(p, T_TWX_C);
-    a.tws = tab<double>(p, T_TWX_S);
-    a.dctc = tab<double>(p, T_DCTX_C);
-    a.dcts = tab<double>(p, T_DCTX_S);
+    set_grad(p, &a, adjoint, dt);
+    a.twc = tab<T>(p, T_TWX_C);
+    a.tws = tab<T>(p, T_TWX_S);
+    a.dctc = tab<T>(p, T_DCTX_C);
+    a.dcts = tab<T>(p, T_DCTX_S);
+    const int ntj = p->ny / kXgRows;
+    a.kc = xg_planes(p, p->nx <= 256 ? 2 : 1, 1);
     const int nchunk = (p->nz + a.kc - 1) / a.kc;
-    const dim3 grid((unsigned)((p->ny / kXgRows) * nchunk));
     Timed t(p, K_XINV_GRAD);
-    if (p->nx == 768)
-        hipLaunchKernelGGL((k_xinv_grad<768>), grid, dim3(xg_threads<768>()), 2 * 768 * sizeof(double), S(p), a);
-    else
-        hipLaunchKernelGGL((k_xinv_grad<512>), grid, dim3(xg_threads<512>()), 2 * 512 * sizeof(double), S(p), a);
+    ops->xg_d(a, (unsigned)(ntj * nchunk), S(p));
 }
 
 // first refinement correction fused with the gradient and the convergence
@@ -323,7 +367,7 @@ long launch_xinv_grad_resid(fsei_plan* p, const float* in, const float* p32, con
     a.nz = p->nz;
     a.bcx = p->bcx;
     a.bcy = p->bcy;
-    a.kc = kXgPlanes;
+    a.kc = xg_planes(p, p->nx == 512 ? 2 : 1, 2);
     a.in = in;
     a.p32 = p32;
     a.vsum = vsum;
@@ -406,20 +450,6 @@ void launch_y(fsei_plan* p, T* data, bool inverse) {
     else if constexpr (sizeof(T) == 8) launch_y_cfg<T, 4096, 512>(p, a, inverse);
 }
 
-// compute units of the current device (cached per device; 256 if the query fails)
-int cus_of_current_device() {
-    constexpr int kDevs = 64;
-    static std::atomic<int> cus[kDevs];
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kDevs) return 256;
-    int n = cus[dev].load(std::memory_order_relaxed);
-    if (n <= 0) {
-        if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) n = 256;
-        cus[dev].store(n, std::memory_order_relaxed);
-    }
-    return n;
-}
-
 template <typename TS, typename TC>
 ZArgs<TS, TC> zargs(const fsei_plan* p, TS* data, int transposed, bool record_mean) {
     ZArgs<TS, TC> a{};
@@ -491,19 +521,7 @@ void launch_grad(fsei_plan* p, const Vel<TIO>& q, const TP* pr, bool adjoint, do
     a.bcy = p->bcy;
     set_vel(&a, q);
     a.p = pr;
-    if (!adjoint) {
-        a.cx = (TIO)(-dt / p->dx);
-        a.cy = (TIO)(-dt / p->dy);
-        a.sw = (TIO)(-dt);
-        a.bk = tab<TIO>(p, T_INV_H);
-        a.gk = tab<TIO>(p, T_INV_H);
-    } else {
-        a.cx = (TIO)(1.0 / p->dx);
-        a.cy = (TIO)(1.0 / p->dy);
-        a.sw = (TIO)1;
-        a.bk = tab<TIO>(p, T_INV_DZ);
-        a.gk = tab<TIO>(p, T_GAM_ADJ);
-    }
+    set_grad(p, &a, adjoint, dt);
     Timed t(p, K_GRAD);
     const bool al = q.aligned() && aligned16(pr);
     const int np = p->nx / 2;
@@ -1071,16 +1089,16 @@ fsei_status project_impl(fsei_plan* p, const Vel<double>& q, double* pout, doubl
     // fused with the gradient (its halo rows must not be overwritten by a
     // neighbouring tile's p), else in the caller's p when given
     double* ws1 = static_cast<double*>(field1(p));
-    const bool fused = xg_ok(p, ws1, pout, q);
-    double* buf = (pout && !fused) ? pout : ws1;
+    const LenOps* xg = xg_ops(p, ws1, pout, q);
+    double* buf = (pout && !xg) ? pout : ws1;
     XFwdArgs<double, double> a = div_args<double, double>(p, q.ui, q.vi, q.wi, nullptr, false, dt);
     a.out = buf;
     launch_xfwd<double, double, PRO_DIV>(p, a, K_XFWD);
     launch_y<double>(p, buf, false);
     launch_z<double>(p, buf, 0, true);
     launch_y<double>(p, buf, true);
-    if (fused) {
-        launch_xinv_grad(p, buf, pout, q, false, dt);
+    if (xg) {
+        launch_xinv_grad(p, xg, buf, pout, q, false, dt);
     } else {
         launch_xinv<double, double, EPI_STORE>(p, buf, buf, K_XINV);
         launch_grad<double, double>(p, q, buf, false, dt);
@@ -1197,8 +1215,8 @@ fsei_status backward_impl(fsei_plan* p, const Vel<double>& q, const double* gp, 
     launch_y<double>(p, buf, false);
     launch_z<double>(p, buf, 1, false);
     launch_y<double>(p, buf, true);
-    if (xg_ok(p, buf, nullptr, q)) {
-        launch_xinv_grad(p, buf, nullptr, q, true, dt);
+    if (const LenOps* xg = xg_ops(p, buf, nullptr, q)) {
+        launch_xinv_grad(p, xg, buf, nullptr, q, true, dt);
     } else {
         launch_xinv<double, double, EPI_STORE>(p, buf, buf, K_XINV);
         launch_grad<double, double>(p, q, buf, true, dt);

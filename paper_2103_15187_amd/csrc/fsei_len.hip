@@ -17,6 +17,10 @@ template <typename T, typename TP, int EPI>
 void xinv(const XInvArgs<T, TP>& a, unsigned grid, hipStream_t st) {
     hipLaunchKernelGGL((k_xinv_len<T, TP, EPI, N>), dim3(grid), dim3(x_len_threads(N, (int)sizeof(T))), 0, st, a);
 }
+template <typename T>
+void xinv_grad(const XInvGradArgs<T>& a, unsigned grid, hipStream_t st) {
+    hipLaunchKernelGGL((k_xinv_grad_len<T, N>), dim3(grid), dim3(XgGeom<N>::NTHR), 0, st, a);
+}
 template <typename T, bool VEC>
 void yfwd(const YArgs<T>& a, unsigned grid, hipStream_t st) {
     hipLaunchKernelGGL((k_yfwd_len<T, N, VEC>), dim3(grid), dim3(y_len_threads(N, (int)sizeof(T))), 0, st, a);
@@ -46,6 +50,7 @@ LenOps make() {
     o.xi_fd[EPI_ACC] = xinv<float, double, EPI_ACC>;
     o.xi_fd[EPI_ADDF] = xinv<float, double, EPI_ADDF>;
     o.xi_fd[EPI_ACC_KEEP] = xinv<float, double, EPI_ACC_KEEP>;
+    if constexpr (xg_len(N)) o.xg_d = xinv_grad<double>;
     o.yf_d[0] = yfwd<double, false>;
     o.yf_d[1] = yfwd<double, true>;
     o.yi_d[0] = yinv<double, false>;

@@ -389,6 +389,175 @@ __global__ __launch_bounds__(x_len_threads(NF, (int)sizeof(T))) void k_xinv_len(
 }
 
 // ---------------------------------------------------------------------------
+// x inverse fused with the gradient correction (paper, Sec. 2.1, eq.
+// NSdiscr0: the pressure term -dt grad p^{n+1} applied to the provisional
+// velocity), even lengths:
+//     p = inverse x transform of the y-inverted field,
+//     u += cx (p_i - p_{i-1}),  v += cy (p_j - p_{j-1}),
+//     w += sw (bk_k p_k - gk_k p_{k-1}),
+// on active faces (wall faces written 0), p written once (optional) and never
+// re-read: 64 bytes per FP64 cell (56 without p) against 72 in two passes.
+// A workgroup owns GR = 8 rows j0..j0+7 (whole tiles only: row tests around
+// the stores cost 40 registers) over a chunk of planes and marches up in z.  Each step inverts the 8
+// rows plus row j0-1 (whose p the v update of row j0 needs) of one plane: 9
+// real rows as 5 complex sequences, the last paired with a zero row.  RG
+// groups of threads, one thread per column pair in each, share the rows of the
+// gradient; the own rows' p of the previous plane stay in registers for the w
+// update; the chunk's first step only produces them (it inverts the plane
+// below the chunk).
+// ---------------------------------------------------------------------------
+template <int NF>
+struct XgGeom {
+    static constexpr int NP = NF / 2;
+    static constexpr int RG = xg_len_groups(NF);
+    static constexpr int RPG = kXgRows / RG;
+    static constexpr int NTHR = xg_len_threads(NF);
+    static constexpr int SP = seq_stride(NF);
+};
+
+template <typename T, int NF>
+__global__ __launch_bounds__(XgGeom<NF>::NTHR) void k_xinv_grad_len(XInvGradArgs<T> a) {
+    using G = XgGeom<NF>;
+    using V = typename Vec2T<T>::type;
+    constexpr int NP = G::NP, RG = G::RG, RPG = G::RPG, NTHR = G::NTHR, SP = G::SP;
+    constexpr int GR = kXgRows, NSQ = kXgSeq;
+    constexpr int GB = RPG < 4 ? RPG : 4;        // rows per batch of the gradient phase
+    constexpr int NSG = (NSQ + RG - 1) / RG;     // sequences a group loads
+    static_assert(NF % 2 == 0 && GR % RG == 0, "column pairs, whole groups");
+    __shared__ T sre[NSQ * SP];
+    __shared__ T sim[NSQ * SP];
+    __shared__ T twl[2 * NF];
+    const int ny = a.ny, nz = a.nz;
+    const int ntj = ny / GR;
+    const int b = (int)xcd_remap(blockIdx.x, gridDim.x);
+    const int chunk = b / ntj;
+    const int j0 = (b - chunk * ntj) * GR;
+    const int kb = chunk * a.kc;
+    const int ke = (kb + a.kc < nz) ? kb + a.kc : nz;
+    const int jh = (j0 > 0) ? j0 - 1 : ny - 1;   // halo row (wrapped; unused for a y wall at j0 = 0)
+    const bool wallx = a.bcx == FSEI_BC_WALL, wally = a.bcy == FSEI_BC_WALL;
+    stage_twiddles<T, NTHR>(twl, a.twc, a.tws, NF);
+    const bool act = threadIdx.x < NP * RG;
+    const int g = act ? (int)threadIdx.x / NP : 0;
+    // pre-processing: column m and its partner nm of every row
+    const int m = act ? (int)threadIdx.x - g * NP : 0;
+    const int nm = (m == 0) ? NF / 2 : NF - m;
+    const int lm = li(0, m, SP), lnm = li(0, nm, SP);
+    T cm = (T)1, sm = (T)0, cn = (T)1, sn = (T)0;
+    if (wallx) {
+        cm = a.dctc[m];
+        sm = a.dcts[m];
+        cn = (m == 0) ? a.dctc[NF / 2] : sm;
+        sn = (m == 0) ? a.dcts[NF / 2] : cm;
+    }
+    // gradient: this thread's column pair (i, i + 1) and the x neighbour i - 1
+    const int i = 2 * m, l0g = g * RPG;
+    const int ixm = (i > 0) ? i - 1 : NF - 1;
+    const int q0 = li(0, wallx ? mk_pos(i, NF) : i, SP);
+    const int q1 = li(0, wallx ? mk_pos(i + 1, NF) : i + 1, SP);
+    const int qm = li(0, wallx ? mk_pos(ixm, NF) : ixm, SP);
+    const size_t plane = (size_t)NF * ny;
+    auto rowj = [&](int l) { return j0 + l; };
+    // p of tile row r (r = 0: the halo row, r = 1..8: the own rows); the
+    // sequence pairs rows 2s and 2s + 1
+    auto pv = [&](int r, int q) -> T { return ((r & 1) ? sim : sre)[(r >> 1) * SP + q]; };
+    V prev[RPG];
+#pragma unroll
+    for (int l = 0; l < RPG; ++l) prev[l].x = prev[l].y = (T)0;
+    // input rows of one step: sequence s = g + t RG of this group's share
+    T xa[NSG][2], xb[NSG][2];
+    auto load_in = [&](int k) {
+        const T* __restrict__ in = a.in + (size_t)k * plane;
+#pragma unroll
+        for (int t = 0; t < NSG; ++t) {
+            const int s = g + t * RG < NSQ ? g + t * RG : NSQ - 1;
+            const T* pa = in + (size_t)(s == 0 ? jh : rowj(2 * s - 1)) * NF;
+            const T* pb = in + (size_t)rowj(2 * s) * NF;
+            xa[t][0] = pa[m];
+            xa[t][1] = pa[nm];
+            xb[t][0] = pb[m];
+            xb[t][1] = pb[nm];
+        }
+    };
+    for (int k = (kb > 0) ? kb - 1 : 0; k < ke; ++k) {
+        if (act) {
+            load_in(k);
+#pragma unroll
+            for (int t = 0; t < NSG; ++t) {
+                const int s = g + t * RG;
+                if (s < NSQ) {
+                    const bool zb = s + 1 == NSQ;    // the last sequence has a zero row
+                    const T b0 = zb ? (T)0 : xb[t][0], b1 = zb ? (T)0 : xb[t][1];
+                    const T pa = (m == 0) ? xa[t][1] : xa[t][0], pb = (m == 0) ? b1 : b0;
+                    T zr, zi;
+                    pre_inv_cs<T>(NF, m, a.bcx, xa[t][0], xa[t][1], b0, b1, cm, sm, zr, zi);
+                    sre[s * SP + lm] = zr;
+                    sim[s * SP + lm] = zi;
+                    pre_inv_cs<T>(NF, nm, a.bcx, xa[t][1], pa, b1, pb, cn, sn, zr, zi);
+                    sre[s * SP + lnm] = zr;
+                    sim[s * SP + lnm] = zi;
+                }
+            }
+        }
+        __syncthreads();
+        fft_fixed<T, NSQ * NF, NTHR, 1, NF, 0, 1>(sre, sim, NSQ, twl, twl + NF);
+        if (!act) {
+        } else if (k >= kb) {   // not the chunk's first (halo) plane
+            const T bkk = a.bk[k], gkk = a.gk[k];
+            const size_t ro = (size_t)k * plane + (size_t)j0 * NF + i;
+            V pym;
+            pym.x = pv(l0g, q0);
+            pym.y = pv(l0g, q1);
+#pragma unroll
+            for (int t0 = 0; t0 < RPG; t0 += GB) {
+                V uo[GB], vo[GB], wo[GB];
+#pragma unroll
+                for (int t = 0; t < GB; ++t) {
+                    const size_t o = (size_t)k * plane + (size_t)rowj(l0g + t0 + t) * NF + i;
+                    uo[t] = *reinterpret_cast<const V*>(a.ui + o);
+                    vo[t] = *reinterpret_cast<const V*>(a.vi + o);
+                    wo[t] = *reinterpret_cast<const V*>(a.wi + o);
+                }
+#pragma unroll
+                for (int t = 0; t < GB; ++t) {
+                    const int l = l0g + t0 + t, r = l + 1;
+                    V pc;
+                    pc.x = pv(r, q0);
+                    pc.y = pv(r, q1);
+                    const T pxm = pv(r, qm);
+                    const int j = j0 + l;
+                    V un, vn, wn;
+                    un.x = (wallx && i == 0) ? (T)0 : uo[t].x + a.cx * (pc.x - pxm);
+                    un.y = uo[t].y + a.cx * (pc.y - pc.x);
+                    const bool v0 = wally && j == 0;
+                    vn.x = v0 ? (T)0 : vo[t].x + a.cy * (pc.x - pym.x);
+                    vn.y = v0 ? (T)0 : vo[t].y + a.cy * (pc.y - pym.y);
+                    wn.x = (k == 0) ? (T)0 : wo[t].x + a.sw * (bkk * pc.x - gkk * prev[t0 + t].x);
+                    wn.y = (k == 0) ? (T)0 : wo[t].y + a.sw * (bkk * pc.y - gkk * prev[t0 + t].y);
+                    // non-temporal: nothing here is read again soon
+                    const size_t o = ro + (size_t)l * NF;
+                    nt_store2(a.u + o, un);
+                    nt_store2(a.v + o, vn);
+                    nt_store2(a.w + o, wn);
+                    if (a.p) nt_store2(a.p + o, pc);
+                    prev[t0 + t] = pc;
+                    pym = pc;
+                }
+                // keep the next batch's loads after this batch's stores
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        } else {
+#pragma unroll
+            for (int t = 0; t < RPG; ++t) {
+                prev[t].x = pv(l0g + t + 1, q0);
+                prev[t].y = pv(l0g + t + 1, q1);
+            }
+        }
+        __syncthreads();   // the next step overwrites the tile
+    }
+}
+
+// ---------------------------------------------------------------------------
 // y transforms: a tile is y_len_pairs adjacent column pairs of one z-plane;
 // a thread owns one pair s and the rows jr, jr + RPP, ...  VEC: pairs as one
 // access (a switch inside the kernel makes the compiler merge both forms into
@@ -582,6 +751,8 @@ using XFwdFn = void (*)(const XFwdArgs<TI, TO>&, unsigned, hipStream_t);
 template <typename T, typename TP>
 using XInvFn = void (*)(const XInvArgs<T, TP>&, unsigned, hipStream_t);
 template <typename T>
+using XgFn = void (*)(const XInvGradArgs<T>&, unsigned, hipStream_t);
+template <typename T>
 using YFn = void (*)(const YArgs<T>&, unsigned, hipStream_t);
 
 struct LenOps {
@@ -593,6 +764,7 @@ struct LenOps {
     XInvFn<double, double> xi_dd[EPI_KINDS];
     XInvFn<float, float> xi_ff[EPI_KINDS];
     XInvFn<float, double> xi_fd[EPI_KINDS];
+    XgFn<double> xg_d;          // null where the fused kernel is not compiled
     YFn<double> yf_d[2], yi_d[2];   // [column pairs as one access]
     YFn<float> yf_f[2], yi_f[2];
     template <typename TI, typename TO>

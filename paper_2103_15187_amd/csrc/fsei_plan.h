@@ -78,6 +78,16 @@ constexpr int x_len_threads(int n, int elem) {
     return (elem == 4 && n <= 768) ? round64(t) : round_waves(t);
 }
 
+// The fused x inverse + gradient kernel (FP64): even lengths from 256 to 768.
+// Two thread groups, one thread per column pair in each, divide its eight rows
+// up to 512 points; enough threads for a radix-8 stage of its five sequences.
+constexpr bool xg_len(int n) { return n % 2 == 0 && n >= 256 && n <= 768; }
+constexpr int xg_len_groups(int n) { return n <= 512 ? 2 : 1; }
+constexpr int xg_len_threads(int n) {
+    const int t = n / 2 * xg_len_groups(n), b = 5 * n / 8;
+    return n <= 512 ? round64(t) : round_waves(t > b ? t : b);
+}
+
 // Tile of the compiled y kernels: column pairs per tile (rows of 128 bytes;
 // 64 for lines beyond 512, two of whose workgroups then fit a CU), about
 // eight complex elements per thread

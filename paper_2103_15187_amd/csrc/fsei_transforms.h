@@ -520,186 +520,41 @@ __global__ __launch_bounds__(NTHR) void k_xinv(XInvArgs<T, TP> a) {
     }
 }
 
-// ---------------------------------------------------------------------------
-// x inverse fused with the gradient correction (paper, Sec. 2.1, eq.
-// NSdiscr0: the pressure term -dt grad p^{n+1} applied to the provisional
-// velocity), FP64, compile-time length NF, one column pair per thread:
-//     p = inverse x transform of the y-inverted field,
-//     u += cx (p_i - p_{i-1}),  v += cy (p_j - p_{j-1}),
-//     w += sw (bk_k p_k - gk_k p_{k-1}),
-// on active faces (wall faces written 0), p written once (optional) and never
-// re-read.  A workgroup owns GR = 8 rows j0..j0+7 over a chunk of planes and
-// marches up in z.  Each step inverts the 8 rows plus row j0-1 (whose p the v
-// update of row j0 needs) of one plane: 9 real rows as 5 complex sequences,
-// the last paired with a zero row.  The own rows' p of the previous plane
-// stay in registers for the w update; the chunk's first step only produces
-// them (it inverts the plane below the chunk).
-// ---------------------------------------------------------------------------
-struct XInvGradArgs {
-    int ny, nz, bcx, bcy, kc;   // kc: planes per chunk
-    const double* in;           // y-inverted field (transform space in x)
-    double* p;                  // pressure out, or null
-    const double* ui;           // velocity in (the outputs, or arrays that overlap none)
-    const double* vi;
-    const double* wi;
-    double* u;                  // velocity out
-    double* v;
-    double* w;
-    double cx, cy, sw;
-    const double* bk;
-    const double* gk;
-    const double* twc;
-    const double* tws;
-    const double* dctc;
-    const double* dcts;
-};
-
 // two adjacent doubles as one non-temporal 16-byte store
 __device__ __forceinline__ void nt_store2(double* q, double2 v) {
     __builtin_nontemporal_store(v.x, q);
     __builtin_nontemporal_store(v.y, q + 1);
 }
-
-constexpr int kXgRows = 8;    // own rows per workgroup
-constexpr int kXgSeq = 5;     // complex sequences per step (8 rows + halo + zero row)
-
-// Threads: one per radix-8 butterfly of a stage (5 NF / 8); the first NF / 2
-// also own one column (pair) each in the load and gradient phases.
-template <int NF>
-constexpr int xg_threads() { return kXgSeq * NF / 8; }
-
-template <int NF>
-__global__ __launch_bounds__(xg_threads<NF>()) void k_xinv_grad(XInvGradArgs a) {
-    constexpr int NTHR = xg_threads<NF>();
-    constexpr int GR = kXgRows, NSQ = kXgSeq, EMAX = NSQ * NF;
-    static_assert(NTHR >= NF / 2, "a column pair per thread");
-    constexpr int SP = seq_stride(NF);
-    constexpr int GB = 4;   // rows per batch of the gradient phase
-    static_assert(NSQ * SP <= lds_elems(EMAX), "tile fits");
-    static_assert(2 * NSQ == GR + 2, "halo row + own rows + one zero row");
-    static_assert(GR % GB == 0, "whole batches");
-    __shared__ double sre[lds_elems(EMAX)];
-    __shared__ double sim[lds_elems(EMAX)];
-    const int ny = a.ny, nz = a.nz;
-    const int ntj = ny / GR;
-    const int b = (int)xcd_remap(blockIdx.x, gridDim.x);
-    const int chunk = b / ntj;
-    const int jt = b - chunk * ntj;
-    const int j0 = jt * GR;
-    const int kb = chunk * a.kc;
-    const int ke = (kb + a.kc < nz) ? kb + a.kc : nz;
-    const int jh = (j0 > 0) ? j0 - 1 : ny - 1;   // halo row (wrapped; unused for a y wall at j0 = 0)
-    const bool wallx = a.bcx == FSEI_BC_WALL, wally = a.bcy == FSEI_BC_WALL;
-    double* twl = lds_twiddles<double, NTHR>(a.twc, a.tws, NF);
-    const bool colt = threadIdx.x < NF / 2;   // owns a column (pair)
-    // pre-processing: column m and its partner nm of every row
-    const int m = colt ? threadIdx.x : 0;
-    const int nm = (m == 0) ? NF / 2 : NF - m;
-    const int lm = li(0, m, SP), lnm = li(0, nm, SP);
-    double cm = 1.0, sm = 0.0, cn = 1.0, sn = 0.0;
-    if (wallx) {
-        cm = a.dctc[m];
-        sm = a.dcts[m];
-        cn = (m == 0) ? a.dctc[NF / 2] : sm;
-        sn = (m == 0) ? a.dcts[NF / 2] : cm;
-    }
-    // gradient: this thread's column pair (i, i + 1) and the x neighbour i - 1
-    const int i = 2 * m;
-    const int ixm = (i > 0) ? i - 1 : NF - 1;
-    const int q0 = li(0, wallx ? mk_pos(i, NF) : i, SP);
-    const int q1 = li(0, wallx ? mk_pos(i + 1, NF) : i + 1, SP);
-    const int qm = li(0, wallx ? mk_pos(ixm, NF) : ixm, SP);
-    const size_t plane = (size_t)NF * ny;
-    // input rows of one step: tile row r = 0 is the halo row, r = 1..8 the
-    // own rows, r = 9 zero; sequence s pairs rows 2s and 2s + 1
-    double xa[NSQ][2], xb[NSQ][2];
-    auto load_in = [&](int k) {
-        const double* __restrict__ in = a.in + (size_t)k * plane;
-#pragma unroll
-        for (int s = 0; s < NSQ; ++s) {
-            const int ra = 2 * s, rb = 2 * s + 1;
-            const double* pa = in + (size_t)((ra == 0) ? jh : j0 + ra - 1) * NF;
-            xa[s][0] = pa[m];
-            xa[s][1] = pa[nm];
-            if (rb <= GR) {
-                const double* pb = in + (size_t)(j0 + rb - 1) * NF;
-                xb[s][0] = pb[m];
-                xb[s][1] = pb[nm];
-            } else {
-                xb[s][0] = 0.0;
-                xb[s][1] = 0.0;
-            }
-        }
-    };
-    auto pv = [&](int r, int q) -> double { return ((r & 1) ? sim : sre)[(r >> 1) * SP + q]; };
-    double2 prev[GR];
-#pragma unroll
-    for (int l = 0; l < GR; ++l) prev[l] = make_double2(0.0, 0.0);
-    int k = (kb > 0) ? kb - 1 : 0;
-    for (; k < ke; ++k) {
-        if (colt) load_in(k);
-#pragma unroll
-        for (int s = 0; s < NSQ && colt; ++s) {
-            const double pa = (m == 0) ? xa[s][1] : xa[s][0], pb = (m == 0) ? xb[s][1] : xb[s][0];
-            double zr, zi;
-            pre_inv_cs<double>(NF, m, a.bcx, xa[s][0], xa[s][1], xb[s][0], xb[s][1], cm, sm, zr, zi);
-            sre[s * SP + lm] = zr;
-            sim[s * SP + lm] = zi;
-            pre_inv_cs<double>(NF, nm, a.bcx, xa[s][1], pa, xb[s][1], pb, cn, sn, zr, zi);
-            sre[s * SP + lnm] = zr;
-            sim[s * SP + lnm] = zi;
-        }
-        __syncthreads();
-        fft_fixed<double, EMAX, NTHR, 1, NF, 0, 1>(sre, sim, NSQ, twl, twl + NF);
-        // the next step's input is in flight during this step's gradient
-        double2 pym = make_double2(pv(0, q0), pv(0, q1));
-        if (!colt) {
-        } else if (k >= kb) {   // not the chunk's first (halo) plane
-            const double bkk = a.bk[k], gkk = a.gk[k];
-            const size_t ro = (size_t)k * plane + (size_t)j0 * NF + i;
-#pragma unroll
-            for (int l0 = 0; l0 < GR; l0 += GB) {
-                double2 uo[GB], vo[GB], wo[GB];
-#pragma unroll
-                for (int t = 0; t < GB; ++t) {
-                    const size_t o = ro + (size_t)(l0 + t) * NF;
-                    uo[t] = *reinterpret_cast<const double2*>(a.ui + o);
-                    vo[t] = *reinterpret_cast<const double2*>(a.vi + o);
-                    wo[t] = *reinterpret_cast<const double2*>(a.wi + o);
-                }
-#pragma unroll
-                for (int t = 0; t < GB; ++t) {
-                    const int l = l0 + t, r = l + 1;
-                    const double2 pc = make_double2(pv(r, q0), pv(r, q1));
-                    const double pxm = pv(r, qm);
-                    const int j = j0 + l;
-                    double2 un, vn, wn;
-                    un.x = (wallx && i == 0) ? 0.0 : uo[t].x + a.cx * (pc.x - pxm);
-                    un.y = uo[t].y + a.cx * (pc.y - pc.x);
-                    const bool v0 = wally && j == 0;
-                    vn.x = v0 ? 0.0 : vo[t].x + a.cy * (pc.x - pym.x);
-                    vn.y = v0 ? 0.0 : vo[t].y + a.cy * (pc.y - pym.y);
-                    wn.x = (k == 0) ? 0.0 : wo[t].x + a.sw * (bkk * pc.x - gkk * prev[l].x);
-                    wn.y = (k == 0) ? 0.0 : wo[t].y + a.sw * (bkk * pc.y - gkk * prev[l].y);
-                    // non-temporal: nothing here is read again soon
-                    const size_t o = ro + (size_t)l * NF;
-                    nt_store2(a.u + o, un);
-                    nt_store2(a.v + o, vn);
-                    nt_store2(a.w + o, wn);
-                    if (a.p) nt_store2(a.p + o, pc);
-                    prev[l] = pc;
-                    pym = pc;
-                }
-                // keep the next batch's loads after this batch's stores
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        } else {
-#pragma unroll
-            for (int l = 0; l < GR; ++l) prev[l] = make_double2(pv(l + 1, q0), pv(l + 1, q1));
-        }
-        __syncthreads();   // the next step overwrites the tile
-    }
+__device__ __forceinline__ void nt_store2(float* q, float2 v) {
+    __builtin_nontemporal_store(v.x, q);
+    __builtin_nontemporal_store(v.y, q + 1);
 }
+
+// own rows per workgroup and complex sequences per step of the fused x
+// inverses (8 rows, the halo row j0 - 1, and a zero row or the halo row j0 + 8)
+constexpr int kXgRows = 8;
+constexpr int kXgSeq = 5;
+
+// the fused x inverse + gradient correction (k_xinv_grad_len)
+template <typename T>
+struct XInvGradArgs {
+    int ny, nz, bcx, bcy, kc;   // kc: planes per chunk
+    const T* in;                // y-inverted field (transform space in x)
+    T* p;                       // pressure out, or null
+    const T* ui;                // velocity in (the outputs, or arrays that overlap none)
+    const T* vi;
+    const T* wi;
+    T* u;                       // velocity out
+    T* v;
+    T* w;
+    T cx, cy, sw;
+    const T* bk;
+    const T* gk;
+    const T* twc;
+    const T* tws;
+    const T* dctc;
+    const T* dcts;
+};
 
 // ---------------------------------------------------------------------------
 // The first correction of the FP32 + FP64 refinement fused with the gradient
@@ -710,7 +565,7 @@ __global__ __launch_bounds__(xg_threads<NF>()) void k_xinv_grad(XInvGradArgs a) 
 //     u += cx (p_i - p_{i-1}),  v += cy (p_j - p_{j-1}),
 //     w += sw (bk_k p_k - gk_k p_{k-1})        (wall faces written 0),
 //     r = (f - mean) - L p,  per-workgroup partials of sum r^2 and sum r,
-// p written once.  The marching of k_xinv_grad, with 10 rows per plane
+// p written once.  The marching of k_xinv_grad_len, with 10 rows per plane
 // (halo rows j0-1 and j0+8, both needed by the Laplacian) as 5 complex FP32
 // sequences.  The residual of plane k needs p of plane k+1: its part
 // without that term is kept in registers and completed one step later (the
@@ -748,7 +603,7 @@ struct XInvGradResArgs {
 // threads of k_xinv_grad_resid: one per column pair at 512 (two workgroups
 // per CU fit the registers), one per radix-8 butterfly at 768
 template <int NF>
-constexpr int xgr_threads() { return NF == 512 ? NF / 2 : xg_threads<NF>(); }
+constexpr int xgr_threads() { return NF == 512 ? NF / 2 : kXgSeq * NF / 8; }
 
 template <int NF>
 __global__ __launch_bounds__(xgr_threads<NF>()) void k_xinv_grad_resid(XInvGradResArgs a) {
