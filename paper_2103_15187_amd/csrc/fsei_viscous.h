@@ -37,7 +37,7 @@ namespace fsei {
 namespace dev {
 
 constexpr int kViscXLines = 8;  // lines per tile of the x kernel
-constexpr int kViscXTiles = 4;  // tiles per workgroup of the x kernel
+constexpr int kViscXTiles = 4;  // most tiles per workgroup of the x kernel
 
 struct ViscArgs {
     double* data;
@@ -49,6 +49,7 @@ struct ViscArgs {
                         // stored over data
     int ncol;           // strided kernel: columns (lines side by side along x)
     long nlines;        // x kernel: number of lines
+    int tiles;          // x kernel: tiles per workgroup
     size_t rstride;     // strided kernel: elements between consecutive rows of a line
     size_t bstride;     // strided kernel: elements between the line groups of blockIdx.y
     int remap;          // strided kernel: workgroups in XCD-contiguous runs (y lines: measured 8 %
@@ -417,67 +418,83 @@ __global__ __launch_bounds__(16 * kViscPmax) void k_visc_strided_pf(ViscArgs a, 
 
 // Contiguous lines (x): tiles of kViscXLines lines staged through LDS
 // (coalesced 16-byte loads and stores when n is even), one lane per (line,
-// chunk); each workgroup walks kViscXTiles consecutive tiles so that the
-// tables are staged once per kViscXTiles tiles.  Dynamic LDS:
-// kViscXLines * (n + 2) doubles.  Grid ceil(nlines / (kViscXLines kViscXTiles)).
+// chunk); each workgroup walks a.tiles (at most kViscXTiles) consecutive tiles
+// so that the tables are staged once for them.  Dynamic LDS:
+// kViscXLines * (n + 2) doubles.  Grid ceil(nlines / (kViscXLines a.tiles)).
 template <int L>
 __global__ __launch_bounds__(kViscXLines * kViscPmax) void k_visc_x(ViscArgs a) {
     constexpr int TXL = kViscXLines, NT = TXL * kViscPmax;
-    constexpr int IPL = (16 * L + NT - 1) / NT;   // 16-byte loads per line and thread (n <= 32 L)
+    constexpr int IPT = (TXL * 16 * L + NT - 1) / NT;   // 16-byte items of a tile per thread (n <= 32 L)
     __shared__ double st[visc_tab_elems(L)];
     __shared__ double sc[2 * NT];
     __shared__ double sx[2 * TXL];
     extern __shared__ __align__(16) unsigned char visc_dyn[];
     double* tile = reinterpret_cast<double*>(visc_dyn);
-    visc_load_tables<L, NT>(a.tab, st);
     const int n = a.n, sp = n + 2, h2 = n / 2;
     const bool vec = a.vec != 0;   // uniform
     const int ln = threadIdx.x % TXL, p = threadIdx.x / TXL;
     const int s0 = p * L;
-    // 16-byte path: the next tile's loads are issued into registers before
-    // the current tile is solved, so they are in flight during the solve
-    // (indices clamped into the tile, so every lane loads unconditionally;
-    // the clamped values are never stored)
+    // 16-byte path, items being pairs of rows.  Where a full line is whole
+    // sets of threads (16 and 32 rows per chunk) a set takes part of one line;
+    // else a tile's lines, contiguous as they are, go to the threads in order,
+    // item q of line l at 2 q + 2 l of the padded tile (96 rows: 48 of 256
+    // lanes worked on a line at a time; 18.7 -> 11.0 us for 96 x 72 x 130, 128 ->
+    // 118 for 288 x 288 x 467; 512 rows so 604 -> 623).  The next tile's items are
+    // loaded into registers before the current tile is solved, so they are in
+    // flight during the solve (items beyond the tile re-read its last one).
+    constexpr bool SETS = (16 * L) % NT == 0;
+    constexpr int IPL = SETS ? 16 * L / NT : 1;   // sets per line
     typedef double d2 __attribute__((ext_vector_type(2)));
-    d2 pre[TXL][IPL];
-#define FSEI_VISC_FETCH(L0, NL)                                                                        \
-    {                                                                                                  \
-        const double* __restrict__ gf = a.data + (size_t)(L0) * n;                                     \
-        _Pragma("unroll") for (int l = 0; l < TXL; ++l) _Pragma("unroll") for (int r = 0; r < IPL; ++r) { \
-            const int lc = (l < (NL)) ? l : (NL) - 1;                                                  \
-            int i2 = threadIdx.x + r * NT;                                                             \
-            i2 = (i2 < h2) ? i2 : h2 - 1;                                                              \
-            pre[l][r] = *reinterpret_cast<const d2*>(gf + (size_t)lc * n + 2 * i2);                    \
-        }                                                                                              \
+    d2 pre[IPT];
+    int slot[IPT];
+#pragma unroll
+    for (int r = 0; r < IPT; ++r) {
+        const int q = threadIdx.x + (SETS ? r % IPL : r) * NT;
+        if constexpr (SETS) slot[r] = (r / IPL) * sp + 2 * (q < h2 ? q : h2 - 1);
+        else slot[r] = 2 * q + 2 * (vec ? q / h2 : 0);
     }
-    long line0 = (long)blockIdx.x * kViscXTiles * TXL;
-    if (vec && line0 < a.nlines) FSEI_VISC_FETCH(line0, ((a.nlines - line0 < TXL) ? (int)(a.nlines - line0) : TXL))
+    auto fetch = [&](long l0) {
+        const int last = (int)((a.nlines - l0 < TXL ? a.nlines - l0 : TXL) * h2) - 1;
+        const d2* __restrict__ gf = reinterpret_cast<const d2*>(a.data + (size_t)l0 * n);
+#pragma unroll
+        for (int r = 0; r < IPT; ++r) {
+            if constexpr (SETS) {
+                const int l = r / IPL, q = threadIdx.x + (r % IPL) * NT;
+                const int nl = (int)(a.nlines - l0 < TXL ? a.nlines - l0 : TXL);
+                pre[r] = (gf + (size_t)(l < nl ? l : nl - 1) * h2)[q < h2 ? q : h2 - 1];
+                continue;
+            }
+            // a uniform base per r, the lane's offset limited to the tile
+            const int left = last - r * NT;
+            const unsigned lim = left > 0 ? left : 0;
+            pre[r] = (gf + (left > 0 ? r * NT : last))[threadIdx.x < lim ? threadIdx.x : lim];
+        }
+    };
+    long line0 = (long)blockIdx.x * a.tiles * TXL;
+    if constexpr (SETS) visc_load_tables<L, NT>(a.tab, st);
+    if (vec && line0 < a.nlines) fetch(line0);
+    if constexpr (!SETS) visc_load_tables<L, NT>(a.tab, st);
     // unrolled: the prefetch registers then stay registers across tiles
 #pragma unroll
     for (int tt = 0; tt < kViscXTiles; ++tt, line0 += TXL) {
-        if (line0 >= a.nlines) break;   // uniform over the workgroup
+        if (tt >= a.tiles || line0 >= a.nlines) break;   // uniform over the workgroup
         const int nl = (a.nlines - line0 < TXL) ? (int)(a.nlines - line0) : TXL;
+        const int items = nl * h2;
         double* __restrict__ g = a.data + (size_t)line0 * n;
         __syncthreads();   // the previous tile's stores have read the tile
         if (vec) {
-            // every register goes to its (clamped) slot: rows past nl are
-            // never read back, a clamped column rewrites its own value
 #pragma unroll
-            for (int l = 0; l < TXL; ++l)
-#pragma unroll
-                for (int r = 0; r < IPL; ++r) {
-                    int i2 = threadIdx.x + r * NT;
-                    i2 = (i2 < h2) ? i2 : h2 - 1;
-                    *reinterpret_cast<d2*>(tile + l * sp + 2 * i2) = pre[l][r];
-                }
+            for (int r = 0; r < IPT; ++r)
+                // (SETS: every register to its clamped slot: rows past nl are
+                // never read back, a clamped column rewrites its own value)
+                if (SETS || (int)threadIdx.x + r * NT < items) *reinterpret_cast<d2*>(tile + slot[r]) = pre[r];
         } else {
             for (int l = 0; l < nl; ++l)
                 for (int i = threadIdx.x; i < n; i += NT) tile[l * sp + i] = g[(size_t)l * n + i];
         }
         __syncthreads();   // tile (and, first time, tables) staged
         const long next = line0 + TXL;
-        if (vec && tt + 1 < kViscXTiles && next < a.nlines)
-            FSEI_VISC_FETCH(next, ((a.nlines - next < TXL) ? (int)(a.nlines - next) : TXL))
+        if (vec && tt + 1 < a.tiles && next < a.nlines) fetch(next);
         double F[1][L];
 #pragma unroll
         for (int t = 0; t < L; ++t) F[0][t] = (s0 + t < n && ln < nl) ? tile[ln * sp + s0 + t] : 0.0;
@@ -488,15 +505,17 @@ __global__ __launch_bounds__(kViscXLines * kViscPmax) void k_visc_x(ViscArgs a) 
                 if (s0 + t < n) tile[ln * sp + s0 + t] = F[0][t];
         }
         __syncthreads();
-#undef FSEI_VISC_FETCH
-        for (int l = 0; l < nl; ++l) {
-            if (vec) {
-                for (int i = 2 * threadIdx.x; i < n; i += 2 * NT)
-                    *reinterpret_cast<double2*>(g + (size_t)l * n + i) =
-                        *reinterpret_cast<const double2*>(tile + l * sp + i);
-            } else {
+        if (vec) {
+#pragma unroll
+            for (int r = 0; r < IPT; ++r)
+                if constexpr (SETS) {
+                    const int l = r / IPL, q = threadIdx.x + (r % IPL) * NT;
+                    if (l < nl && q < h2) reinterpret_cast<d2*>(g)[l * h2 + q] = *reinterpret_cast<const d2*>(tile + slot[r]);
+                } else if ((int)threadIdx.x + r * NT < items)
+                    reinterpret_cast<d2*>(g)[threadIdx.x + r * NT] = *reinterpret_cast<const d2*>(tile + slot[r]);
+        } else {
+            for (int l = 0; l < nl; ++l)
                 for (int i = threadIdx.x; i < n; i += NT) g[(size_t)l * n + i] = tile[l * sp + i];
-            }
         }
     }
 }
