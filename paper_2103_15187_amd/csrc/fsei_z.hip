@@ -15,7 +15,7 @@ constexpr bool F32 = sizeof(T) == 4;
 
 // All forms do the same arithmetic.  ZPF: the persistent kernel; ZV: adjacent
 // modes per lane as one vector; Z1: one mode per lane; the number: chunks.
-enum ZForm { ZPF1, ZPF32, ZV32, ZV32_WIDE, ZV64, Z1_32, Z1_64 };
+enum ZForm { ZPF1, ZPF32, ZV32_HALF, ZV32, ZV32_WIDE, ZV64, Z1_32, Z1_64 };
 
 // chunking of the z lines: P chunks of exactly L rows (L one of the compiled
 // sizes), the last chunk padded with decoupled rows; P <= pmax
@@ -125,6 +125,13 @@ bool z_tiling<T>(Args* a, int cus) {
         a->form = ZPF32;
         tx = pf_modes(*a);
         nt = 32 * pf_lanes(a->L);
+    } else if (F32 && c32 && a->L <= 16 && nx % 2 == 0) {
+        // 16 lanes x 2 modes (128-B rows) in 512 threads: half the registers
+        // of the next form, so twice its waves per CU (us: 384 x 384 x 500 166
+        // -> 155, 288 x 288 x 467 81 -> 67, 128 x 128 x 192 18.6 -> 16.6; at 24
+        // rows 218 -> 299)
+        a->form = ZV32_HALF;
+        tx = 32;
     } else if (c32 && a->L <= 24 && nx % (16 / (int)sizeof(T)) == 0) {
         // FP64: 16 lanes x 2 modes (256-B rows) in 512 threads.  FP32: 8 lanes
         // x 4 modes (128-B rows) in 256 threads, two workgroups per CU, one
@@ -191,6 +198,9 @@ void z_launch<T>(const Args& a, hipStream_t st, int cus) {
                 else if (a.transposed) launch_pf<24, 12, false, true>(a, st, cus);
                 else launch_pf<24, 12, false, false>(a, st, cus);
             }
+            break;
+        case ZV32_HALF:
+            if constexpr (F32) launch_v<2, 16, 512, false>(a, st);
             break;
         case ZV32:
             if constexpr (F32) launch_v<4, 8, 256, false>(a, st);
