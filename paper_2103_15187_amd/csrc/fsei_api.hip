@@ -198,7 +198,11 @@ long launch_xfwd(fsei_plan* p, XFwdArgs<TI, TO> a, int slot) {
     const bool al = al16(a.u) && al16(a.v) && al16(a.w) && al16(a.gp) && al16(a.f) && al16(a.p) &&
                     al16(a.p32) && al16(a.out) && al16(a.out_f);
     Timed t(p, slot);
-    if (const LenOps* o = x_ops(p, al)) {
+    const LenOps* o = x_ops(p, al);
+    // without room for a partial sum per tile (some plans of lines beyond 768
+    // and ny no multiple of 4): the kernel whose tiles run on across planes
+    if (o && a.partials && x_len_blocks(p, o) > (long)p->n_partials) o = nullptr;
+    if (o) {
         const long nb = x_len_blocks(p, o);
         o->xfwd<TI, TO>(PRO)(a, (unsigned)nb, S(p));
         return nb;

@@ -61,7 +61,11 @@ void compute_layout(fsei_plan_impl* p) {
     // residual-norm pass, whichever is more
     p->n_partials = (size_t)std::max(((long)p->ny * p->nz + 2 * nseq - 1) / (2 * nseq),
                                      (long)((p->ny + 7) / 8) * p->nz);
-    if (p->nx <= kLenMax) {
+    // Their tiles end at planes: up to nz triples more (ny no multiple of the
+    // rows).  Not where there are no near-singular lines to speak of: the room
+    // is that of their former scratch, so a workspace is nowhere larger than it
+    // was and no plan leaves the limit of the fixed scratch (launch_xfwd).
+    if (p->nx <= kLenMax && p->nlist >= 2) {
         const int nl = x_len_rows(p->nx);
         p->n_partials = std::max(p->n_partials, (size_t)((p->ny + nl - 1) / nl) * p->nz);
     }
