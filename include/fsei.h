@@ -113,9 +113,8 @@ fsei_status fsei_plan_workspace_size(const fsei_plan* plan, size_t* bytes);
 
 /* Hand the plan a device buffer of at least fsei_plan_workspace_size bytes,
  * 256-byte aligned.  Uploads the metric, eigenvalue and twiddle tables with a
- * synchronous copy, and on the first call creates the plan's side stream and
- * two events on the current device (see Execution above).  The buffer stays
- * owned by the caller and must outlive its use by the plan. */
+ * synchronous copy.  The buffer stays owned by the caller and must outlive its
+ * use by the plan. */
 fsei_status fsei_plan_set_workspace(fsei_plan* plan, void* device_ptr, size_t bytes);
 
 /* Stream (a hipStream_t passed as void*) on which all work is enqueued. NULL =
