@@ -40,17 +40,16 @@ TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic_c3_512x512x768.json")
 # Kernel that each timing slot launches at the 512 x 512 x 768 workload (the
 # hardware-counter summary is keyed by kernel name)
 SLOT_KERNEL = {
-    "fp64": {"xfwd": "k_xfwd<double, double, 1, 2048, 256, 512>", "yfwd": "k_yfwd<double, 4096, 512, 512, 4>",
-             "zsolve": "k_zsolvev_pf<double, double, 2, 16, 24, 512, 12>", "yinv": "k_yinv<double, 4096, 512, 512, 4>",
-             "xinv": "k_xinv<double, double, 0, 2048, 256, 512>", "grad": "k_grad_row2<double, double, 256, 16>",
-             "xinv_grad": "k_xinv_grad<512>"},
-    "fp32_refine": {"xfwd": "k_xfwd<double, float, 1, 2048, 256, 512>", "yfwd": "k_yfwd<float, 8192, 1024, 512, 6>",
-                    "zsolve": "k_zsolvev_pf<float, float, 4, 16, 24, 512, 12>", "yinv": "k_yinv<float, 8192, 1024, 512, 4>",
-                    "xinv": "k_xinv<float, float, 0, 2048, 256, 512>", "xinv_acc": "k_xinv<float, double, 2, 2048, 256, 512>",
-                    "resid": "k_resid_pairs<256, 8, true, float, 2>",
-                    "resid_norm": "k_resid_pairs<256, 8, false, double, 2>",
-                    "xfwd_r": "k_xfwd<float, float, 4, 2048, 256, 512>", "grad": "k_grad_row2<double, double, 256, 16>",
-                    "grad_resid": "k_grad_resid<256, 16, false>", "xinv_grad_resid": "k_xinv_grad_resid<512>"},
+    "fp64": {"xfwd": "k_xfwd_len<double, double, 1, 512>", "yfwd": "k_yfwd_len<double, 512, true>",
+             "zsolve": "k_zsolvev_pf<double, double, 2, 16, 24, 512, 12, false, false>",
+             "yinv": "k_yinv_len<double, 512, true>",
+             "xinv_grad": "k_xinv_grad_len<double, 512>"},
+    "fp32_refine": {"xfwd": "k_xfwd_len<double, float, 1, 512>", "yfwd": "k_yfwd_len<float, 512, true>",
+                    "zsolve": "k_zsolvev_pf<float, float, 4, 16, 24, 512, 12, false, false>",
+                    "yinv": "k_yinv_len<float, 512, true>",
+                    "xinv": "k_xinv_len<float, float, 0, 512>",
+                    "resid_xfwd": "k_xfwd_len<double, float, 4, 512>",
+                    "xinv_grad_resid": "k_xinv_grad_resid<512>"},
     "viscous_fp64": {"visc_x": "k_visc_x<16>", "visc_y": "k_visc_strided<2, 16>",
                      "visc_z": "k_visc_strided_pf<24, 12>"},
     "momentum_fp64": {"momentum_rhs": "k_momentum_rhs_pairs<64, 16, true>"},
