@@ -434,7 +434,6 @@ __global__ __launch_bounds__(XgGeom<NF>::NTHR) void k_xinv_grad_len(XInvGradArgs
     const int j0 = (b - chunk * ntj) * GR;
     const int kb = chunk * a.kc;
     const int ke = (kb + a.kc < nz) ? kb + a.kc : nz;
-    const int jh = (j0 > 0) ? j0 - 1 : ny - 1;   // halo row (wrapped; unused for a y wall at j0 = 0)
     const bool wallx = a.bcx == FSEI_BC_WALL, wally = a.bcy == FSEI_BC_WALL;
     stage_twiddles<T, NTHR>(twl, a.twc, a.tws, NF);
     const bool act = threadIdx.x < NP * RG;
@@ -471,8 +470,8 @@ __global__ __launch_bounds__(XgGeom<NF>::NTHR) void k_xinv_grad_len(XInvGradArgs
 #pragma unroll
         for (int t = 0; t < NSG; ++t) {
             const int s = g + t * RG < NSQ ? g + t * RG : NSQ - 1;
-            const T* pa = in + (size_t)(s == 0 ? jh : rowj(2 * s - 1)) * NF;
-            const T* pb = in + (size_t)rowj(2 * s) * NF;
+            const T* pa = in + (size_t)xg_in_row(s, 0, j0, ny) * NF;
+            const T* pb = in + (size_t)xg_in_row(s, 1, j0, ny) * NF;
             xa[t][0] = pa[m];
             xa[t][1] = pa[nm];
             xb[t][0] = pb[m];

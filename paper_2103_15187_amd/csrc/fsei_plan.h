@@ -88,6 +88,18 @@ constexpr int xg_len_threads(int n) {
     return n <= 512 ? round64(t) : round_waves(t > b ? t : b);
 }
 
+// Own rows and complex sequences per step of the fused x inverses, and the row
+// of a plane that sequence s (0 .. kXgSeq - 1) of the x inverse + gradient reads
+// as its first (half 0) or second (half 1) line, for the tile of rows j0 ..
+// j0 + 7: sequence 0 starts with the halo row j0 - 1 (wrapped); the last one's
+// second line is a zero row, for which a valid row is addressed.
+constexpr int kXgRows = 8;
+constexpr int kXgSeq = 5;
+constexpr int xg_in_row(int s, int half, int j0, int ny) {
+    return half == 0 ? (s == 0 ? (j0 > 0 ? j0 - 1 : ny - 1) : j0 + 2 * s - 1)
+                     : j0 + (2 * s < kXgRows ? 2 * s : kXgRows - 1);
+}
+
 // Tile of the compiled y kernels: column pairs per tile (rows of 128 bytes;
 // 64 for lines beyond 512, two of whose workgroups then fit a CU), about
 // eight complex elements per thread

@@ -530,11 +530,6 @@ __device__ __forceinline__ void nt_store2(float* q, float2 v) {
     __builtin_nontemporal_store(v.y, q + 1);
 }
 
-// own rows per workgroup and complex sequences per step of the fused x
-// inverses (8 rows, the halo row j0 - 1, and a zero row or the halo row j0 + 8)
-constexpr int kXgRows = 8;
-constexpr int kXgSeq = 5;
-
 // the fused x inverse + gradient correction (k_xinv_grad_len)
 template <typename T>
 struct XInvGradArgs {
