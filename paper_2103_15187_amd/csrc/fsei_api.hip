@@ -665,11 +665,7 @@ fsei_status check_hip() {
 // ---------------------------------------------------------------------------
 template <int L>
 void launch_visc_x_L(fsei_plan* p, ViscArgs a) {
-    // several tiles per workgroup (tables staged once) where eight workgroups
-    // per CU remain; with four tiles each, 9360 lines of 96 rows made 293
-    // workgroups and took 17 us
-    const long want = 8L * cus_of_current_device() * kViscXLines;
-    a.tiles = (int)std::max(1L, std::min((long)kViscXTiles, a.nlines / want));
+    a.tiles = visc_x_tiles(a.nlines, a.n, L, cus_of_current_device());
     const long per = (long)kViscXLines * a.tiles;
     const unsigned nb = (unsigned)((a.nlines + per - 1) / per);
     const int dyn = kViscXLines * (a.n + 2) * (int)sizeof(double);

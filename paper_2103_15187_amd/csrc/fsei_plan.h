@@ -127,6 +127,37 @@ constexpr int visc_chunk(int n) {
                                  : 0;
 }
 
+// The x kernel of the line solves: tiles of kViscXLines lines, one lane per
+// (line, chunk), each workgroup walking up to kViscXTiles consecutive tiles with
+// the tables staged once.
+constexpr int kViscXLines = 8;
+constexpr int kViscXTiles = 4;
+// its workgroups per CU, by LDS (tables, scan slots and the tile) and threads
+constexpr long visc_x_per_cu(int n, int L) {
+    const long lds = 8L * (visc_tab_elems(L) + 2 * kViscXLines * kViscPmax + 2 * kViscXLines + kViscXLines * (n + 2));
+    const long fit = 160L * 1024 / lds, thr = 2048 / (kViscXLines * kViscPmax);
+    return fit < thr ? fit : thr;
+}
+// Twice the time of nlines lines with t tiles per workgroup, in tiles: the
+// tables and the first tile's round trip cost about 2.5 tiles more per workgroup
+// (measured one round: 96 rows 5.1 + 1.5 t us, 512 rows 7.3 + 2.8 t, 768 rows
+// 9.8 + 3.8 t)
+constexpr long visc_x_cost(long nlines, int t, int n, int L, int cus) {
+    const long per = (long)kViscXLines * t, slots = visc_x_per_cu(n, L) * cus;
+    const long groups = (nlines + per - 1) / per;
+    return (groups + slots - 1) / slots * (2 * t + 5);
+}
+// Tiles per workgroup: the fewest such tiles in all rounds of the CUs.  (us
+// with 1, 2, 3, 4 tiles: 7968 lines of 768 rows, one workgroup per CU, 47.0,
+// 38.7, 43.9, 30.3; 24000 lines of 512 rows 47.1, 47.4, 42.2, 45.4; 9360 lines
+// of 96 rows 11, 12, 13, 15.)
+constexpr int visc_x_tiles(long nlines, int n, int L, int cus) {
+    int best = 1;
+    for (int t = 2; t <= kViscXTiles; ++t)
+        if (visc_x_cost(nlines, t, n, L, cus) < visc_x_cost(nlines, best, n, L, cus)) best = t;
+    return best;
+}
+
 // Radix schedule of one complex FFT length (radices 8, 4, 2, 3).
 struct FftPlan {
     int n = 0;

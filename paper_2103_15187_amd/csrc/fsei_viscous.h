@@ -30,14 +30,11 @@
 
 #include <hip/hip_runtime.h>
 
-#include "fsei_plan.h"   // kViscPmax, kViscLv, visc_tab_elems
+#include "fsei_plan.h"   // kViscPmax, kViscLv, kViscXLines, kViscXTiles, visc_tab_elems
 #include "fsei_transforms.h"   // xcd_remap
 
 namespace fsei {
 namespace dev {
-
-constexpr int kViscXLines = 8;  // lines per tile of the x kernel
-constexpr int kViscXTiles = 4;  // most tiles per workgroup of the x kernel
 
 struct ViscArgs {
     double* data;
