@@ -1470,10 +1470,14 @@ fsei_status fsei_ib_spread(fsei_plan* p, int comp, double* field, const double* 
     a.dvb = dvb;
     {
         Timed t(p, K_IB);
-        if (p->ncells() <= (size_t)0xFFFFFFFEu)   // node offsets fit the LDS table's 32-bit keys
-            hipLaunchKernelGGL(k_ib_spread_lds, dim3((unsigned)((nb + 255) / 256)), dim3(256), 0, S(p), a);
+        const dim3 grid((unsigned)((nb + 255) / 256));
+        // the LDS table's 32-bit keys must hold the node offsets
+        if (p->ncells() > (size_t)0xFFFFFFFEu)
+            hipLaunchKernelGGL(k_ib_spread<size_t>, grid, dim3(256), 0, S(p), a);
+        else if (nb <= 256L * cus_of_current_device())
+            hipLaunchKernelGGL(k_ib_spread_lds<true>, grid, dim3(256), 0, S(p), a);
         else
-            hipLaunchKernelGGL(k_ib_spread<size_t>, dim3((unsigned)((nb + 255) / 256)), dim3(256), 0, S(p), a);
+            hipLaunchKernelGGL(k_ib_spread_lds<false>, grid, dim3(256), 0, S(p), a);
     }
     return check_hip();
 }

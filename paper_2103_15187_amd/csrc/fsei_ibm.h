@@ -210,12 +210,22 @@ __global__ __launch_bounds__(256) void k_ib_spread(IbArgs a) {
 // whose tables leave two workgroups per CU, 144 and 176 us).  Markers that share
 // no nodes: 1.23 -> 1.06 ms per million.  Needs 32-bit offsets: the empty key
 // is no run number.
+//
+// FEW: at most one workgroup per CU, so that the launch takes as long as one
+// marker's chain of probes, and longest where markers share no nodes and the
+// table overflows.  There a probe is one compare-and-swap (no read first), four
+// probes look for a slot, and a marker that found none adds the rest of its runs
+// directly.  Markers apart / on one
+// surface / at one point, 4000 each, us: 18 / 17 / 19 (as for many markers 37 /
+// 37 / 18, and 34 / 34 / 23 with a key per node).  With many markers the reads
+// and the eight probes are the faster: 998 200 on the surface 131 against 157.
 constexpr int kIbRun = 4;
 constexpr int kIbSlots = 1024;   // runs in the table: 36 KB, four workgroups per CU
-constexpr int kIbProbes = 8;
 constexpr unsigned kIbEmpty = 0xFFFFFFFFu;
 
+template <bool FEW>
 __global__ __launch_bounds__(256) void k_ib_spread_lds(IbArgs a) {
+    constexpr int PROBES = FEW ? 4 : 8;
     __shared__ unsigned skey[kIbSlots];
     __shared__ double sval[kIbSlots * kIbRun];
     for (int t = threadIdx.x; t < kIbSlots; t += 256) skey[t] = kIbEmpty;
@@ -224,8 +234,8 @@ __global__ __launch_bounds__(256) void k_ib_spread_lds(IbArgs a) {
     // slot of a run, or -1
     auto find = [&](unsigned run) -> int {
         unsigned h = (run * 2654435761u) / (unsigned)(0x100000000ull / kIbSlots);
-        for (int pr = 0; pr < kIbProbes; ++pr) {
-            unsigned old = *(volatile unsigned*)&skey[h];   // most finds meet their run
+        for (int pr = 0; pr < PROBES; ++pr) {
+            unsigned old = FEW ? kIbEmpty : *(volatile unsigned*)&skey[h];   // (many: most finds meet their run)
             if (old == kIbEmpty) old = atomicCAS(&skey[h], kIbEmpty, run);
             if (old == kIbEmpty || old == run) return (int)h;
             h = (h + 1) % kIbSlots;
@@ -236,6 +246,7 @@ __global__ __launch_bounds__(256) void k_ib_spread_lds(IbArgs a) {
     if (b < a.nb) {
         const IbSupport s = ib_support(a, b);
         const double f = a.fb[b] * a.dvb[b] / (a.dx * a.dy);
+        bool look = true;
 #pragma unroll
         for (int kk = 0; kk < 3; ++kk) {
             const double fk = f / a.hz[s.z.idx[kk]] * s.z.n[kk];
@@ -250,7 +261,8 @@ __global__ __launch_bounds__(256) void k_ib_spread_lds(IbArgs a) {
                     const double v = ib_share(s, fk * s.y.n[jj], ii, jj, kk);
                     if (key / kIbRun != run) {
                         run = key / kIbRun;
-                        slot = find(run);
+                        slot = look ? find(run) : -1;
+                        if (FEW) look = slot >= 0;
                     }
                     if (slot >= 0) atomicAdd(&sval[slot * kIbRun + key % kIbRun], v);
                     else atomicAdd(a.field + key, v);
