@@ -121,10 +121,19 @@ __device__ __forceinline__ void renorm2(double& n0, double& d0, double& n1, doub
 template <int NT>
 constexpr int zspec_threads() { return NT < 512 ? NT : 512; }
 // chunks and rows per chunk of the special lines beside tiles of pmax chunks of
-// l rows: twice as many half as long for 16 rows and more (a lane holds two
+// l rows: twice as many half as long for 8 rows and more (a lane holds two
 // FP64 values per row; with 24 rows the tiles' kernels spilled)
-constexpr int zspec_chunks(int pmax, int l) { return l <= 12 ? pmax : 2 * pmax; }
-constexpr int zspec_rows(int l) { return l <= 12 ? l : l / 2; }
+constexpr int zspec_chunks(int pmax, int l) { return l <= 4 ? pmax : 2 * pmax; }
+constexpr int zspec_rows(int l) { return l <= 4 ? l : l / 2; }
+// Waves per SIMD that the tile code reaches by itself and that the special
+// lines, compiled into the same kernel, must leave it (m modes per lane; 0: no
+// bound needed): without a bound they took the registers of the FP32 kernels from
+// 37-62 to 50-104 and a workgroup per CU with them (486 x 243 x 144, two
+// modes per lane in 1024 threads: 47 -> 67 us).
+constexpr int z_waves(int elem, int m, int l) {
+    return elem == 8 ? (m == 1 && l == 4 ? 8 : 0)
+                     : m == 1 ? (l <= 12 ? 8 : 0) : m == 2 ? (l <= 8 ? 8 : l == 12 ? 6 : 0) : 0;
+}
 template <int PMAX, int L, int NT>
 constexpr int zspec_lds() { return (2 * PMAX * L + 4 * zspec_threads<NT>()) * (int)sizeof(double); }
 
@@ -373,7 +382,7 @@ __global__ __launch_bounds__(512, 4) void k_zspecial(ZArgs<TS, TC> a) {
 }
 
 template <typename TS, typename TC, int TXL, int L, int NT>
-__global__ __launch_bounds__(NT) void k_zsolve(ZArgs<TS, TC> a) {
+__global__ __launch_bounds__(NT, z_waves(sizeof(TC), 1, L)) void k_zsolve(ZArgs<TS, TC> a) {
     constexpr int PMAX = NT / TXL;
     struct Lds {
         TC sh[4][NT];
@@ -558,7 +567,7 @@ template <> struct VecM<float, 2> { typedef float type __attribute__((ext_vector
 template <> struct VecM<float, 4> { typedef float type __attribute__((ext_vector_type(4))); };
 
 template <typename TS, typename TC, int M, int TXLM, int L, int NT>
-__global__ __launch_bounds__(NT) void k_zsolvev(ZArgs<TS, TC> a) {
+__global__ __launch_bounds__(NT, z_waves(sizeof(TC), M, L)) void k_zsolvev(ZArgs<TS, TC> a) {
     using V = typename VecM<TS, M>::type;
     constexpr int PMAX = NT / TXLM;
     struct Lds {

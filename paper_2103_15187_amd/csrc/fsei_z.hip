@@ -95,6 +95,23 @@ void launch_spec(const Args& a, hipStream_t st) {
     hipLaunchKernelGGL((k_zspecial<T, T, PS, L>), dim3(1u + (unsigned)((a.nlist + LN - 1) / LN)), dim3(512), 0, st, a);
 }
 
+// FP32: 16 lanes x 2 modes (128-B rows) in 512 threads against the forms after it
+// in z_tiling's list.  It needs half the registers of the four-mode form and has
+// twice its waves (us: 384 x 384 x 144 54 -> 44, 512 x 512 x 64 58 -> 50, 1024 x
+// 1024 x 64 207 -> 181, 128 x 128 x 192 17.7 -> 15.9), which it loses in many
+// rounds of 12 and 16 rows per chunk (1024 x 1024 x 384 853 -> 918; 512 x 512 x
+// 500 247 -> 265, but 288 x 288 x 500 78 -> 67).  Where nx / 2 is odd the
+// two-mode form in 1024 threads is as fast or faster up to 8 rows (486 x 486 x
+// 256 121 against 145, x 128 82 against 86) but for few tiles (54 x 54 x 200 12.4
+// against 10.8) or few chunks (162 x 162 x 12 10.8 against 9.2).
+bool two_modes_512(const Args& a, int cus) {
+    const long tiles = (long)((a.nx + 31) / 32) * a.ny;
+    if (a.L > 16 || a.nx % 2 != 0) return false;
+    if (a.L >= 12) return tiles <= (a.L == 12 ? 100L : 20L) * cus;
+    if (a.nx % 4 == 0) return true;
+    return a.L == 4 ? (a.P <= 12 || tiles <= 2L * cus) : tiles <= cus;
+}
+
 }  // namespace
 
 // Adjacent modes per lane as one vector where nx allows, at most 32 chunks per
@@ -125,11 +142,7 @@ bool z_tiling<T>(Args* a, int cus) {
         a->form = ZPF32;
         tx = pf_modes(*a);
         nt = 32 * pf_lanes(a->L);
-    } else if (F32 && c32 && a->L <= 16 && nx % 2 == 0) {
-        // 16 lanes x 2 modes (128-B rows) in 512 threads: half the registers
-        // of the next form, so twice its waves per CU (us: 384 x 384 x 500 166
-        // -> 155, 288 x 288 x 467 81 -> 67, 128 x 128 x 192 18.6 -> 16.6; at 24
-        // rows 218 -> 299)
+    } else if (F32 && c32 && two_modes_512(*a, cus)) {
         a->form = ZV32_HALF;
         tx = 32;
     } else if (c32 && a->L <= 24 && nx % (16 / (int)sizeof(T)) == 0) {
