@@ -101,8 +101,9 @@ struct ZArgs {
 // launch of its own on a second stream took about 40 us between its
 // neighbours, 7 us now.
 //
-// LDS: 2 PS L + 4 NTS doubles.  Threads beyond NTS repeat the work of the
-// first NTS (same values to the same slots) and do not store.
+// LDS: ca (2 PS L doubles: the a_k, then the c_k) and ex ([4][NTS] doubles).
+// Threads beyond NTS repeat the work of the first NTS (same values to the same
+// slots) and do not store.
 // ---------------------------------------------------------------------------
 // n and d (or two columns of them) scaled by a common power of two, d near 1
 __device__ __forceinline__ void renorm(double& n, double& d) {
@@ -121,10 +122,13 @@ __device__ __forceinline__ void renorm2(double& n0, double& d0, double& n1, doub
 template <int NT>
 constexpr int zspec_threads() { return NT < 512 ? NT : 512; }
 // chunks and rows per chunk of the special lines beside tiles of pmax chunks of
-// l rows: twice as many half as long for 8 rows and more (a lane holds two
-// FP64 values per row; with 24 rows the tiles' kernels spilled)
-constexpr int zspec_chunks(int pmax, int l) { return l <= 4 ? pmax : 2 * pmax; }
-constexpr int zspec_rows(int l) { return l <= 4 ? l : l / 2; }
+// l rows in nt threads: twice as many half as long for 8 rows and more (a lane
+// holds two FP64 values per row; with 24 rows the tiles' kernels spilled), four
+// times for 24 and more in the 128 registers of 1024 threads (FP32, 162 x 162 x
+// 1800: 176 us without special lines, 257 beside chunks of half the rows)
+constexpr int zspec_split(int l, int nt) { return l <= 4 ? 1 : nt == 1024 && l >= 24 ? 4 : 2; }
+constexpr int zspec_chunks(int pmax, int l, int nt) { return pmax * zspec_split(l, nt); }
+constexpr int zspec_rows(int l, int nt) { return l / zspec_split(l, nt); }
 // Waves per SIMD that the tile code reaches by itself and that the special
 // lines, compiled into the same kernel, must leave it (m modes per lane; 0: no
 // bound needed): without a bound they took the registers of the FP32 kernels from
@@ -134,16 +138,17 @@ constexpr int z_waves(int elem, int m, int l) {
     return elem == 8 ? (m == 1 && l == 4 ? 8 : 0)
                      : m == 1 ? (l <= 12 ? 8 : 0) : m == 2 ? (l <= 8 ? 8 : l == 12 ? 6 : 0) : 0;
 }
-template <int PMAX, int L, int NT>
-constexpr int zspec_lds() { return (2 * PMAX * L + 4 * zspec_threads<NT>()) * (int)sizeof(double); }
+// the bytes of their two LDS arrays
+template <int NT>
+constexpr int zspec_ex() { return 4 * zspec_threads<NT>() * (int)sizeof(double); }
+template <int PMAX, int L>
+constexpr int zspec_tab() { return 2 * PMAX * L * (int)sizeof(double); }
 
 template <typename TS, typename TC, int PS, int L, int NT>
-__device__ __forceinline__ void z_lines(const ZArgs<TS, TC>& a, int grp, double* lds) {
+__device__ __forceinline__ void z_lines(const ZArgs<TS, TC>& a, int grp, double* ca, double* ex) {
     constexpr int NTS = zspec_threads<NT>(), LN = NTS / PS;
     static_assert(LN >= 1 && NTS % PS == 0 && NT % NTS == 0, "whole lines per group");
-    double* ca = lds;
-    double* cc = lds + PS * L;
-    double* ex = lds + 2 * PS * L;   // [4][NTS]
+    double* cc = ca + PS * L;
     const int nz = a.nz;
     for (int k = threadIdx.x; k < PS * L; k += NT) {
         ca[k] = (k > 0 && k < nz) ? a.za64[k] : 0.0;
@@ -363,11 +368,15 @@ __device__ __forceinline__ void z_zero_mode(const ZArgs<TS, TC>& a, double* sh) 
 }
 
 // group g of the special lines, by a whole workgroup of a kernel whose tiles
-// have PMAX chunks of L rows
+// have PMAX chunks of L rows, in two of the tiles' LDS arrays.  (Two arrays and
+// not one block: as parts of one block the compiler takes
+// the tables and the exchange slots of the tile code for aliases, which spilled
+// 30 registers more in the FP32 kernel of 32 rows.)
 template <typename TS, typename TC, int PMAX, int L, int NT>
-__device__ __forceinline__ void z_special(const ZArgs<TS, TC>& a, int g, void* lds) {
-    if (g == 0) z_zero_mode<TS, TC, NT>(a, static_cast<double*>(lds));
-    else z_lines<TS, TC, zspec_chunks(PMAX, L), zspec_rows(L), NT>(a, g - 1, static_cast<double*>(lds));
+__device__ __forceinline__ void z_special(const ZArgs<TS, TC>& a, int g, void* tab, void* ex) {
+    if (g == 0) z_zero_mode<TS, TC, NT>(a, static_cast<double*>(ex));
+    else z_lines<TS, TC, zspec_chunks(PMAX, L, NT), zspec_rows(L, NT), NT>(a, g - 1, static_cast<double*>(tab),
+                                                                       static_cast<double*>(ex));
 }
 
 // The special lines by themselves, where they are more than one group per CU:
@@ -376,27 +385,22 @@ __device__ __forceinline__ void z_special(const ZArgs<TS, TC>& a, int g, void* l
 // launch, 10.73 ms so)
 template <typename TS, typename TC, int PS, int L>
 __global__ __launch_bounds__(512, 4) void k_zspecial(ZArgs<TS, TC> a) {
-    __shared__ double lds[zspec_lds<PS, L, 512>() / sizeof(double)];
-    if (blockIdx.x == 0) z_zero_mode<TS, TC, 512>(a, lds);
-    else z_lines<TS, TC, PS, L, 512>(a, blockIdx.x - 1, lds);
+    __shared__ double tab[2 * PS * L], ex[4 * 512];
+    if (blockIdx.x == 0) z_zero_mode<TS, TC, 512>(a, ex);
+    else z_lines<TS, TC, PS, L, 512>(a, blockIdx.x - 1, tab, ex);
 }
 
 template <typename TS, typename TC, int TXL, int L, int NT>
 __global__ __launch_bounds__(NT, z_waves(sizeof(TC), 1, L)) void k_zsolve(ZArgs<TS, TC> a) {
     constexpr int PMAX = NT / TXL;
-    struct Lds {
-        TC sh[4][NT];
-        TC ta[PMAX * L], tc[PMAX * L], tb[PMAX * L], tm[PMAX * L], tsi[PMAX * L], tso[PMAX * L];
-    };
-    static_assert(sizeof(Lds) >= zspec_lds<PMAX, L, NT>(), "the special lines fit the tile's LDS");
-    __shared__ __align__(16) unsigned char lds[sizeof(Lds)];
+    __shared__ __align__(16) TC sh[4][NT];
+    __shared__ __align__(16) TC tabs[6][PMAX * L];
+    static_assert(sizeof(sh) >= zspec_ex<NT>() && sizeof(tabs) >= zspec_tab<PMAX, L>(), "the special lines fit");
     if ((int)blockIdx.x < a.nspec) {
-        z_special<TS, TC, PMAX, L, NT>(a, blockIdx.x, lds);
+        z_special<TS, TC, PMAX, L, NT>(a, blockIdx.x, tabs, sh);
         return;
     }
-    Lds& sm = *reinterpret_cast<Lds*>(lds);
-    auto& sh = sm.sh;
-    TC *ta = sm.ta, *tc = sm.tc, *tb = sm.tb, *tm = sm.tm, *tsi = sm.tsi, *tso = sm.tso;
+    TC *ta = tabs[0], *tc = tabs[1], *tb = tabs[2], *tm = tabs[3], *tsi = tabs[4], *tso = tabs[5];
     const int nx = a.nx, nz = a.nz, P = a.P;
     const int npad = P * L;
     // per-k coefficients staged in LDS, padded to P*L rows with decoupled
@@ -570,19 +574,14 @@ template <typename TS, typename TC, int M, int TXLM, int L, int NT>
 __global__ __launch_bounds__(NT, z_waves(sizeof(TC), M, L)) void k_zsolvev(ZArgs<TS, TC> a) {
     using V = typename VecM<TS, M>::type;
     constexpr int PMAX = NT / TXLM;
-    struct Lds {
-        TC sh[4][M * NT];
-        TC ta[PMAX * L], tc[PMAX * L], tb[PMAX * L], tm[PMAX * L], tsi[PMAX * L], tso[PMAX * L];
-    };
-    static_assert(sizeof(Lds) >= zspec_lds<PMAX, L, NT>(), "the special lines fit the tile's LDS");
-    __shared__ __align__(16) unsigned char lds[sizeof(Lds)];
+    __shared__ __align__(16) TC sh[4][M * NT];
+    __shared__ __align__(16) TC tabs[6][PMAX * L];
+    static_assert(sizeof(sh) >= zspec_ex<NT>() && sizeof(tabs) >= zspec_tab<PMAX, L>(), "the special lines fit");
     if ((int)blockIdx.x < a.nspec) {
-        z_special<TS, TC, PMAX, L, NT>(a, blockIdx.x, lds);
+        z_special<TS, TC, PMAX, L, NT>(a, blockIdx.x, tabs, sh);
         return;
     }
-    Lds& sm = *reinterpret_cast<Lds*>(lds);
-    auto& sh = sm.sh;
-    TC *ta = sm.ta, *tc = sm.tc, *tb = sm.tb, *tm = sm.tm, *tsi = sm.tsi, *tso = sm.tso;
+    TC *ta = tabs[0], *tc = tabs[1], *tb = tabs[2], *tm = tabs[3], *tsi = tabs[4], *tso = tabs[5];
     const int nx = a.nx, nz = a.nz, P = a.P;
     const int npad = P * L;
     for (int k = threadIdx.x; k < npad; k += NT) {
@@ -814,18 +813,20 @@ __global__ __launch_bounds__(NT) void k_zsolvev_pf(ZArgs<TS, TC> a) {
     constexpr int NZ = P * L;
     typedef __attribute__((address_space(3))) void* lds_void;
     typedef const __attribute__((address_space(1))) void* glb_void;
+    // (one block here: as arrays of their own the FP64 transposed 768-row solve
+    // took 700 us at 512 x 512 x 768 instead of 669, the FP32 one 5 % longer)
     struct Lds {
         TC sh[4][M * NT];
-        TC ta[NZ], tc[NZ], tb[NZ], tso[NZ], tsi[TR ? NZ : 1];
+        TC tabs[TR ? 5 : 4][NZ];
         V pf[S][NT];
     };
-    static_assert(sizeof(Lds) >= zspec_lds<P, L, NT>(), "the special lines fit the tile's LDS");
+    static_assert(sizeof(Lds::sh) >= zspec_ex<NT>() && sizeof(Lds::tabs) >= zspec_tab<P, L>(), "the special lines fit");
     __shared__ __align__(16) unsigned char lds[sizeof(Lds)];
-    for (int g = blockIdx.x; g < a.nspec; g += gridDim.x) z_special<TS, TC, P, L, NT>(a, g, lds);
     Lds& sm = *reinterpret_cast<Lds*>(lds);
     auto& sh = sm.sh;
     auto& pf = sm.pf;
-    TC *ta = sm.ta, *tc = sm.tc, *tb = sm.tb, *tso = sm.tso, *tsi = sm.tsi;
+    for (int g = blockIdx.x; g < a.nspec; g += gridDim.x) z_special<TS, TC, P, L, NT>(a, g, sm.tabs, sm.sh);
+    TC *ta = sm.tabs[0], *tc = sm.tabs[1], *tb = sm.tabs[2], *tso = sm.tabs[3], *tsi = sm.tabs[TR ? 4 : 0];
     const int nx = a.nx, nz = RAG ? a.nz : NZ;
     for (int k = threadIdx.x; k < NZ; k += NT) {
         const bool in = k < nz;   // padding rows: decoupled, diagonal sigma - 1 (never 0)

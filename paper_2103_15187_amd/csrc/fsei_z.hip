@@ -37,7 +37,7 @@ int pf_modes(const Args& a) { return pf_lanes(a.L) * 16 / (int)sizeof(T); }
 
 // groups of special lines beside tiles of pmax chunks in workgroups of nt threads
 int groups(const Args& a, int pmax, int nt) {
-    const int ln = (nt < 512 ? nt : 512) / zspec_chunks(pmax, a.L);
+    const int ln = (nt < 512 ? nt : 512) / zspec_chunks(pmax, a.L, nt);
     return 1 + (a.nlist + ln - 1) / ln;
 }
 
