@@ -539,7 +539,15 @@ void launch_grad(fsei_plan* p, const Vel<TIO>& q, const TP* pr, bool adjoint, do
             launch_grad_row2<TIO, TP, 8>(p, a, grid, np);
         return;
     }
-    hipLaunchKernelGGL((k_grad<TIO, TP>), dim3((unsigned)((long)p->ny * p->nz)), dim3(256), 0, S(p), a);
+    // a row of up to 256 columns has one per thread: registers for four cost it
+    // waves (us, FP64: 27 x 1296 x 315 224 with two, 289 with four; 81 x 432 x 514
+    // 216 and 271); longer rows keep more loads in flight with four (384 x 324 x
+    // 300 386 against 397)
+    const dim3 grid((unsigned)((long)p->ny * p->nz));
+    if (p->nx <= 256)
+        hipLaunchKernelGGL((k_grad<TIO, TP, 2>), grid, dim3(256), 0, S(p), a);
+    else
+        hipLaunchKernelGGL((k_grad<TIO, TP, 4>), grid, dim3(256), 0, S(p), a);
 }
 
 // FP64 residual norm pass of the refinement (partials of sum r^2, sum r,

@@ -8,8 +8,8 @@
 //              refinement) fused with the forward x transform
 //   k_yfwd   : per tile of x-columns of one z-plane, forward y transform
 //   k_zsolve : per (kx, ky) mode, the z tridiagonal, partitioned over the
-//              threads of a workgroup (no global scratch)
-//              the near-singular lines and the singular (0,0) mode in the same launch
+//              threads of a workgroup (no global scratch); the near-singular
+//              lines and the singular (0,0) mode in the same launch
 //   k_yinv, k_xinv : inverse transforms (x inverse writes or accumulates p)
 //   k_grad   : gradient correction of the three velocity components
 #pragma once
@@ -46,7 +46,7 @@ struct GradArgs {
     const TIO* gk;
 };
 
-template <typename TIO, typename TP>
+template <typename TIO, typename TP, int B>
 __global__ __launch_bounds__(256) void k_grad(GradArgs<TIO, TP> a) {
     // one x-row (k, j) per workgroup in XCD-contiguous order.  When ny is a
     // multiple of GJ the rows go in tiles of GJ rows, plane by plane inside a
@@ -71,9 +71,8 @@ __global__ __launch_bounds__(256) void k_grad(GradArgs<TIO, TP> a) {
     const TP* __restrict__ p = a.p;
     const TIO bk = a.bk[k], gk = a.gk[k];
     const size_t jm = (j > 0) ? (size_t)nx : (size_t)0 - (size_t)(ny - 1) * nx;   // offset to row j-1
-    // four columns per thread and batch, every load before the first store
-    // (the outputs may be the inputs, so the compiler cannot move them)
-    constexpr int B = 4;
+    // B columns per thread and batch, every load before the first store (the
+    // outputs may be the inputs, so the compiler cannot move them)
     for (int i0 = threadIdx.x; i0 < nx; i0 += B * 256) {
         TIO pc[B], px[B], py[B], pz[B], uo[B], vo[B], wo[B];
 #pragma unroll
