@@ -169,7 +169,9 @@ fsei_status fsei_project_backward(fsei_plan* plan, double* gu, double* gv, doubl
 
 /* As fsei_project and fsei_project_backward, with the result in arrays of its
  * own: the inputs are only read.  Each output is either its own input (in
- * place) or an array that overlaps no input, no other output and not p. */
+ * place) or an array that overlaps none of u, v, w (gu, gv, gw), no other
+ * output and not p, and p overlaps none of them: FSEI_ERR_ARG otherwise.  gp may
+ * lie anywhere. */
 fsei_status fsei_project_to(fsei_plan* plan, const double* u, const double* v, const double* w, double* u_out,
                             double* v_out, double* w_out, double* p, double dt, fsei_info* info);
 fsei_status fsei_project_backward_to(fsei_plan* plan, const double* gu, const double* gv, const double* gw,

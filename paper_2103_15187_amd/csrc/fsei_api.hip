@@ -739,6 +739,29 @@ fsei_status ready(const fsei_plan* p) {
 
 bool good_dt(double dt) { return std::isfinite(dt) && dt > 0.0; }
 
+// Whether some output of an out-of-place call shares memory with an input other
+// than its own, with another output or with p (its own input: the same array, or
+// none of its memory).  A kernel would read there what another tile has written.
+// dLoss/dp of the adjoint may lie anywhere: it is read before the first output.
+template <typename T>
+bool overlaps(const fsei_plan* p, const Vel<T>& q, const T* pout) {
+    const size_t bytes = p->ncells() * sizeof(T);
+    auto meet = [&](const void* a, const void* b) {
+        const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+        return a != nullptr && b != nullptr && (x < y ? y - x : x - y) < bytes;
+    };
+    const T* in[3] = {q.ui, q.vi, q.wi};
+    const T* out[3] = {q.u, q.v, q.w};
+    for (int i = 0; i < 3; ++i) {
+        if (meet(pout, in[i]) || meet(pout, out[i])) return true;
+        for (int j = 0; j < 3; ++j) {
+            if (j != i && (meet(out[i], in[j]) || meet(out[i], out[j]))) return true;
+            if (j == i && out[i] != in[i] && meet(out[i], in[i])) return true;
+        }
+    }
+    return false;
+}
+
 // the argument checks every projection entry point shares
 template <typename T>
 fsei_status check_vel(const fsei_plan* p, const Vel<T>& q, double dt) {
@@ -1167,12 +1190,15 @@ fsei_status scratch_of_current_device(void** out) {
 extern "C" {
 
 fsei_status fsei_project(fsei_plan* p, double* u, double* v, double* w, double* pout, double dt, fsei_info* info) {
-    return fsei_project_to(p, u, v, w, u, v, w, pout, dt, info);
+    const Vel<double> q = in_place(u, v, w);
+    fsei_status st = check_vel(p, q, dt);
+    return st == FSEI_OK ? project_impl(p, q, pout, dt, info) : st;
 }
 
 fsei_status fsei_project_to(fsei_plan* p, const double* u, const double* v, const double* w, double* ou, double* ov,
                             double* ow, double* pout, double dt, fsei_info* info) {
     const Vel<double> q{u, v, w, ou, ov, ow};
+    if (p && overlaps(p, q, (const double*)pout)) return FSEI_ERR_ARG;
     fsei_status st = check_vel(p, q, dt);
     return st == FSEI_OK ? project_impl(p, q, pout, dt, info) : st;
 }
@@ -1268,34 +1294,43 @@ fsei_status backward_f32_impl(fsei_plan* p, const Vel<float>& q, const float* gp
 extern "C" {
 
 fsei_status fsei_project_backward(fsei_plan* p, double* gu, double* gv, double* gw, const double* gp, double dt) {
-    return fsei_project_backward_to(p, gu, gv, gw, gp, gu, gv, gw, dt);
+    const Vel<double> q = in_place(gu, gv, gw);
+    fsei_status st = check_vel(p, q, dt);
+    return st == FSEI_OK ? backward_impl(p, q, gp, dt) : st;
 }
 
 fsei_status fsei_project_backward_to(fsei_plan* p, const double* gu, const double* gv, const double* gw,
                                      const double* gp, double* ou, double* ov, double* ow, double dt) {
     const Vel<double> q{gu, gv, gw, ou, ov, ow};
+    if (p && overlaps(p, q, (const double*)nullptr)) return FSEI_ERR_ARG;
     fsei_status st = check_vel(p, q, dt);
     return st == FSEI_OK ? backward_impl(p, q, gp, dt) : st;
 }
 
 fsei_status fsei_project_f32(fsei_plan* p, float* u, float* v, float* w, float* pout, float dt) {
-    return fsei_project_to_f32(p, u, v, w, u, v, w, pout, dt);
+    const Vel<float> q = in_place(u, v, w);
+    fsei_status st = check_vel(p, q, dt);
+    return st == FSEI_OK ? project_f32_impl(p, q, pout, dt) : st;
 }
 
 fsei_status fsei_project_to_f32(fsei_plan* p, const float* u, const float* v, const float* w, float* ou, float* ov,
                                 float* ow, float* pout, float dt) {
     const Vel<float> q{u, v, w, ou, ov, ow};
+    if (p && overlaps(p, q, (const float*)pout)) return FSEI_ERR_ARG;
     fsei_status st = check_vel(p, q, dt);
     return st == FSEI_OK ? project_f32_impl(p, q, pout, dt) : st;
 }
 
 fsei_status fsei_project_backward_f32(fsei_plan* p, float* gu, float* gv, float* gw, const float* gp, float dt) {
-    return fsei_project_backward_to_f32(p, gu, gv, gw, gp, gu, gv, gw, dt);
+    const Vel<float> q = in_place(gu, gv, gw);
+    fsei_status st = check_vel(p, q, dt);
+    return st == FSEI_OK ? backward_f32_impl(p, q, gp, dt) : st;
 }
 
 fsei_status fsei_project_backward_to_f32(fsei_plan* p, const float* gu, const float* gv, const float* gw,
                                          const float* gp, float* ou, float* ov, float* ow, float dt) {
     const Vel<float> q{gu, gv, gw, ou, ov, ow};
+    if (p && overlaps(p, q, (const float*)nullptr)) return FSEI_ERR_ARG;
     fsei_status st = check_vel(p, q, dt);
     return st == FSEI_OK ? backward_f32_impl(p, q, gp, dt) : st;
 }
