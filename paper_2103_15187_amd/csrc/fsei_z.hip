@@ -19,8 +19,9 @@ enum ZForm { ZPF1, ZPF32, ZV32_HALF, ZV32, ZV32_WIDE, ZV64, Z1_32, Z1_64 };
 
 // chunking of the z lines: P chunks of exactly L rows (L one of the compiled
 // sizes), the last chunk padded with decoupled rows; P <= pmax
+constexpr int next_rows(int l) { return l < 16 ? l + 4 : l + 8; }   // 4, 8, 12, 16, 24, 32
 bool choose_chunks(Args* a, int pmax) {
-    for (int l : {4, 8, 12, 16, 24, 32}) {
+    for (int l = 4; l <= 32; l = next_rows(l)) {
         const int pc = (a->nz + l - 1) / l;
         if (pc <= pmax) {
             a->L = l;
@@ -61,32 +62,25 @@ void launch_pf_any(const Args& a, hipStream_t st, int cus) {
     }
 }
 
-template <int M, int TXLM, int NT, bool LONG>
+// LO .. HI: the rows per chunk that the tiling gives a form
+template <int M, int TXLM, int NT, int LO, int HI, int L = LO>
 void launch_v(const Args& a, hipStream_t st) {
-    const dim3 g((unsigned)a.nspec + (unsigned)a.gx * (unsigned)a.ny), b(NT);
-    switch (a.L) {
-        case 4: hipLaunchKernelGGL((k_zsolvev<T, T, M, TXLM, 4, NT>), g, b, 0, st, a); break;
-        case 8: hipLaunchKernelGGL((k_zsolvev<T, T, M, TXLM, 8, NT>), g, b, 0, st, a); break;
-        case 12: hipLaunchKernelGGL((k_zsolvev<T, T, M, TXLM, 12, NT>), g, b, 0, st, a); break;
-        case 16: hipLaunchKernelGGL((k_zsolvev<T, T, M, TXLM, 16, NT>), g, b, 0, st, a); break;
-        case 24: hipLaunchKernelGGL((k_zsolvev<T, T, M, TXLM, 24, NT>), g, b, 0, st, a); break;
-        default:
-            if constexpr (LONG) hipLaunchKernelGGL((k_zsolvev<T, T, M, TXLM, 32, NT>), g, b, 0, st, a);
-            break;
+    if (L < HI && a.L != L) {
+        if constexpr (L < HI) launch_v<M, TXLM, NT, LO, HI, next_rows(L)>(a, st);
+        return;
     }
+    const dim3 g((unsigned)a.nspec + (unsigned)a.gx * (unsigned)a.ny), b(NT);
+    hipLaunchKernelGGL((k_zsolvev<T, T, M, TXLM, L, NT>), g, b, 0, st, a);
 }
 
-template <int TXL, int NT>
+template <int TXL, int NT, int LO, int HI, int L = LO>
 void launch_1(const Args& a, hipStream_t st) {
-    const dim3 g((unsigned)a.nspec + (unsigned)a.gx * (unsigned)a.ny), b(NT);
-    switch (a.L) {
-        case 4: hipLaunchKernelGGL((k_zsolve<T, T, TXL, 4, NT>), g, b, 0, st, a); break;
-        case 8: hipLaunchKernelGGL((k_zsolve<T, T, TXL, 8, NT>), g, b, 0, st, a); break;
-        case 12: hipLaunchKernelGGL((k_zsolve<T, T, TXL, 12, NT>), g, b, 0, st, a); break;
-        case 16: hipLaunchKernelGGL((k_zsolve<T, T, TXL, 16, NT>), g, b, 0, st, a); break;
-        case 24: hipLaunchKernelGGL((k_zsolve<T, T, TXL, 24, NT>), g, b, 0, st, a); break;
-        default: hipLaunchKernelGGL((k_zsolve<T, T, TXL, 32, NT>), g, b, 0, st, a); break;
+    if (L < HI && a.L != L) {
+        if constexpr (L < HI) launch_1<TXL, NT, LO, HI, next_rows(L)>(a, st);
+        return;
     }
+    const dim3 g((unsigned)a.nspec + (unsigned)a.gx * (unsigned)a.ny), b(NT);
+    hipLaunchKernelGGL((k_zsolve<T, T, TXL, L, NT>), g, b, 0, st, a);
 }
 
 template <int PS, int L>
@@ -221,25 +215,25 @@ void z_launch<T>(const Args& a, hipStream_t st, int cus) {
             }
             break;
         case ZV32_HALF:
-            if constexpr (F32) launch_v<2, 16, 512, false>(a, st);
+            if constexpr (F32) launch_v<2, 16, 512, 4, 16>(a, st);
             break;
         case ZV32:
-            if constexpr (F32) launch_v<4, 8, 256, false>(a, st);
-            else launch_v<2, 16, 512, false>(a, st);
+            if constexpr (F32) launch_v<4, 8, 256, 12, 24>(a, st);   // up to 8 rows: ZV32_HALF
+            else launch_v<2, 16, 512, 4, 24>(a, st);
             break;
         case ZV32_WIDE:
-            if constexpr (F32) launch_v<2, 32, 1024, false>(a, st);
+            if constexpr (F32) launch_v<2, 32, 1024, 4, 24>(a, st);
             break;
         case ZV64:
-            if constexpr (F32) launch_v<2, 16, 1024, true>(a, st);
+            if constexpr (F32) launch_v<2, 16, 1024, 16, 32>(a, st);   // from 769 rows
             break;
         case Z1_32:
-            if constexpr (F32) launch_1<32, 1024>(a, st);
-            else launch_1<16, 512>(a, st);
+            if constexpr (F32) launch_1<32, 1024, 4, 32>(a, st);
+            else launch_1<16, 512, 4, 32>(a, st);
             break;
         default:
-            if constexpr (F32) launch_1<16, 1024>(a, st);
-            else launch_1<8, 512>(a, st);
+            if constexpr (F32) launch_1<16, 1024, 24, 32>(a, st);   // from 1025 rows
+            else launch_1<8, 512, 24, 32>(a, st);
             break;
     }
 }
