@@ -574,11 +574,11 @@ struct YGeom {
 };
 
 template <typename T, int NF, bool VEC>
-__global__ __launch_bounds__(y_len_threads(NF, (int)sizeof(T)), y_len_waves(NF, (int)sizeof(T))) void k_yfwd_len(YArgs<T> a) {
+__global__ __launch_bounds__(y_len_threads(NF, (int)sizeof(T)), y_len_waves(NF, (int)sizeof(T), false)) void k_yfwd_len(YArgs<T> a) {
     using G = YGeom<T, NF>;
     using V2 = typename Vec2T<T>::type;
     constexpr int NSF = G::NSF, NTHR = G::NTHR, RPP = G::RPP, NPASS = G::NPASS;
-    constexpr int PS = yfwd_pad<T>(), SP = seq_stride(NF, PS);
+    constexpr int PS = y_len_pad((int)sizeof(T), false), SP = seq_stride(NF, PS);
     // FP32: both twiddle tables in LDS first (the tile's registers are the
     // limit: 1024 threads, two workgroups per CU); FP64: post-twiddles in
     // registers, the FFT twiddles' round trip overlaps the tile loads.  (A
@@ -588,6 +588,7 @@ __global__ __launch_bounds__(y_len_threads(NF, (int)sizeof(T)), y_len_waves(NF, 
     __shared__ T sre[NSF * SP];
     __shared__ T sim[NSF * SP];
     __shared__ T twl[(TL ? 4 : 2) * NF];
+    static_assert(sizeof(sre) + sizeof(sim) + sizeof(twl) == y_len_lds(NF, (int)sizeof(T), false), "as the bound has it");
     const int nx = a.nx;
     // tiles in XCD-contiguous runs: two neighbouring tiles that share
     // 128-byte lines meet in one L2
@@ -657,7 +658,7 @@ __global__ __launch_bounds__(y_len_threads(NF, (int)sizeof(T)), y_len_waves(NF, 
 }
 
 template <typename T, int NF, bool VEC>
-__global__ __launch_bounds__(y_len_threads(NF, (int)sizeof(T)), y_len_waves(NF, (int)sizeof(T))) void k_yinv_len(YArgs<T> a) {
+__global__ __launch_bounds__(y_len_threads(NF, (int)sizeof(T)), y_len_waves(NF, (int)sizeof(T), true)) void k_yinv_len(YArgs<T> a) {
     using G = YGeom<T, NF>;
     using V2 = typename Vec2T<T>::type;
     constexpr int NSF = G::NSF, NTHR = G::NTHR, RPP = G::RPP, NPASS = G::NPASS;
@@ -668,6 +669,7 @@ __global__ __launch_bounds__(y_len_threads(NF, (int)sizeof(T)), y_len_waves(NF, 
     __shared__ T sre[NSF * SP];
     __shared__ T sim[NSF * SP];
     __shared__ T twl[2 * NF];
+    static_assert(sizeof(sre) + sizeof(sim) + sizeof(twl) == y_len_lds(NF, (int)sizeof(T), true), "as the bound has it");
     const int nx = a.nx;
     const int bx = (int)xcd_remap(blockIdx.x, gridDim.x);
     const int k = bx / a.ntile;

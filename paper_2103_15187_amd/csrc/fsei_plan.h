@@ -101,12 +101,24 @@ constexpr int xg_in_row(int s, int half, int j0, int ny) {
 }
 
 // Tile of the compiled y kernels: column pairs per tile (rows of 128 bytes;
-// 64 for lines beyond 512, two of whose workgroups then fit a CU), about
+// 64 for lines beyond 512, two of whose workgroups then fit a CU, but for 1024
+// points in FP64 and in the FP32 forward kernel, which reads four tables), about
 // eight complex elements per thread
 constexpr int y_len_pairs(int n, int elem) { return (n <= 512 ? 64 : 32) / elem; }
 constexpr int y_len_threads(int n, int elem) { return round_waves(y_len_pairs(n, elem) * n / 8); }
-// waves per SIMD that two workgroups per CU need (the kernels' register bound)
-constexpr int y_len_waves(int n, int elem) { return (2 * y_len_threads(n, elem) + 255) / 256; }
+// pad of the kernels' LDS sequences: FP32 forward tiles run fastest with one
+// slot per 64 elements, the others with one per 16 (measured)
+constexpr int y_len_pad(int elem, bool inverse) { return elem == 4 && !inverse ? 6 : kPadShift; }
+// their LDS: the tile's two arrays, the FFT twiddles and (FP32 forward) the
+// post-twiddles
+constexpr int y_len_lds(int n, int elem, bool inverse) {
+    return (2 * y_len_pairs(n, elem) * seq_stride(n, y_len_pad(elem, inverse)) + (elem == 4 && !inverse ? 4 : 2) * n) * elem;
+}
+// waves per SIMD that two workgroups per CU need, where two fit (the kernels'
+// register bound)
+constexpr int y_len_waves(int n, int elem, bool inverse) {
+    return ((2 * y_len_lds(n, elem, inverse) <= 160 * 1024 ? 2 : 1) * y_len_threads(n, elem) + 255) / 256;
+}
 
 // Line solves of the implicit viscous step: every line is cut into
 // kViscPmax chunks of L rows (L one of the compiled sizes), so lines of up

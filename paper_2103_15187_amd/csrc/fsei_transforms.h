@@ -222,11 +222,6 @@ __device__ __forceinline__ void post_fwd_v(int bc, bool lo, T zr, T zi, T cr, T 
     }
 }
 
-// LDS pad of the compiled-length y forward kernels: FP32 tiles run fastest with
-// one pad slot per 64 elements, FP64 tiles with one per 16 (measured)
-template <typename T>
-constexpr int yfwd_pad() { return sizeof(T) == 4 ? 6 : kPadShift; }
-
 // s_waitcnt immediates (vmcnt in bits 3:0 and 15:14, expcnt 6:4, lgkmcnt
 // 11:8): wait until at most n vector-memory operations of this wave are
 // outstanding; wait for this wave's LDS operations only
