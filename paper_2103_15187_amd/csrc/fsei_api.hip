@@ -355,9 +355,14 @@ void launch_xinv_grad(fsei_plan* p, const LenOps* ops, const double* in, double*
     ops->xg_d(a, (unsigned)(ntj * nchunk), S(p));
 }
 
-// first refinement correction fused with the gradient and the convergence
-// check (FP32 correction, FP64 p): nx of a compiled length, whole 8-row
-// tiles, every field 16-byte aligned; returns the number of partials written
+// First refinement correction fused with the gradient and the convergence
+// check (FP32 correction, FP64 p): the two lengths it is compiled for, whole 8-row
+// tiles, every field 16-byte aligned; returns the number of partials written.
+// Other lengths take two passes of 80 B/cell instead of 72 (256 x 256 x 384 to
+// 648 x 648 x 300: 4.6 to 5.1 TB/s).  The grid's size is not looked at: against
+// the two passes 512 x 512 x 768 takes 2.88 ms instead of 3.14, 512 x 256 x 256
+// 480 us instead of 514 and 768 x 128 x 128 182 instead of 203, but 512 x 64 x 64
+// 74 instead of 36 and 768 x 64 x 64 82 instead of 48.
 bool xgr_ok(const fsei_plan* p, const void* in, const void* p32, const void* p64, const void* f,
             const Vel<double>& q) {
     return (p->nx == 512 || p->nx == 768) && p->ny % kXgRows == 0 && aligned16(in) && aligned16(p32) &&
